@@ -1402,7 +1402,7 @@ lv_status lv_diffuse(const lv_scene* sc, const lv_graph* gc, const void* g0, lv_
   const size_t sig = dtype_size(dtype) * (size_t)(g->n > 0 ? g->n : 1) * D;
   HIP_TRY(g->b0.ensure(sig, s));
   HIP_TRY(g->b1.ensure(sig, s));
-  HIP_TRY(g->norms.ensure(sizeof(float) * (size_t)D * (steps + 1), s));
+  HIP_TRY(g->norms.ensure(sizeof(float) * diffuse_norm_floats(D, steps), s));
   if (order && !g->ordered) {
     // P A P^T along the Morton order of the scene's centres; any permutation
     // gives the same result, so the order is built once per graph.

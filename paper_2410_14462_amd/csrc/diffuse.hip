@@ -10,6 +10,8 @@ namespace lv {
 
 namespace {
 
+constexpr int kNormSlots = 64;
+
 template <lv_dtype DT>
 __device__ __forceinline__ float ld(const void* p, int64_t i) {
   if constexpr (DT == LV_F32) return static_cast<const float*>(p)[i];
@@ -27,10 +29,72 @@ __device__ __forceinline__ void st(void* p, int64_t i, float x) {
   }
 }
 
-// Squared column norms of g [n][D] into nrm [D] (pre-zeroed).
+// Squared norms are accumulated in `slots` copies of a [D] row, block b adding
+// to copy b mod slots, and a step sums the copies of the norms it divides by.
+// Atomics on one address complete one after the other, about 15 ns each, so
+// the thousands of blocks of a step that add to the same words are held up by
+// them: on a million rows of 13.6 edges a D = 64 BF16 step took 248 us with
+// one copy and 202 with 64, the column norms of a D = 1 signal 59 us and 16.
+// Wide rows spread over addresses by themselves; their copies are cut so that
+// a block's sum of them stays at 16 KB of reads.
+inline int norm_slots(int D) {
+  int s = kNormSlots;
+  while (s > 1 && (int64_t)s * D > 4096) s >>= 1;
+  return s;
+}
+
+// Sum over the slots of channel ch, the same in every block (a fixed order);
+// threads t, t + C, ... of the block's 256 hold the same channel, C a power of
+// two up to 64.  red: 4 C floats of LDS.
+template <int C>
+__device__ __forceinline__ float slot_sum(const float* __restrict__ nrm, int slots, int D, int ch,
+                                          float* red) {
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  float v = 0.0f;
+  if (ch < D)
+    for (int k = t / C; k < slots; k += 256 / C) v += nrm[(int64_t)k * D + ch];
+#pragma unroll
+  for (int off = C; off < 64; off <<= 1) v += __shfl_xor(v, off, 64);
+  if (lane < C) red[w * C + lane] = v;
+  __syncthreads();
+  const int c = t & (C - 1);
+  const float r = (red[c] + red[C + c]) + (red[2 * C + c] + red[3 * C + c]);
+  __syncthreads();
+  return r;
+}
+
+// Squared column norms of g [n][D], D <= 64, into the slots of nrm
+// (pre-zeroed): 256 / D rows at a time per block, consecutive threads on
+// consecutive elements.
+template <lv_dtype DT>
+__global__ __launch_bounds__(256) void colnorm_flat_kernel(const void* __restrict__ g, int64_t n, int D,
+                                                           int slots, float* __restrict__ nrm) {
+  __shared__ float part[256];
+  const int t = threadIdx.x, rows = 256 / D;
+  const int64_t step = (int64_t)gridDim.x * rows;
+  float s = 0.0f;
+  if (t < rows * D) {
+    const int c = t % D;
+#pragma unroll 4
+    for (int64_t r = (int64_t)blockIdx.x * rows + t / D; r < n; r += step) {
+      const float x = ld<DT>(g, r * D + c);
+      s = __builtin_fmaf(x, x, s);
+    }
+  }
+  part[t] = s;
+  __syncthreads();
+  if (t < D) {
+    float a = 0.0f;
+    for (int q = t; q < rows * D; q += D) a += part[q];
+    if (a != 0.0f) atomicAdd(&nrm[(int64_t)(blockIdx.x % (unsigned)slots) * D + t], a);
+  }
+}
+
+// The same for any D, 64 channels per grid row.
 template <lv_dtype DT>
 __global__ __launch_bounds__(256) void colnorm_kernel(const void* __restrict__ g, int64_t n, int D,
-                                                      int rows_per_block, float* __restrict__ nrm) {
+                                                      int rows_per_block, int slots,
+                                                      float* __restrict__ nrm) {
   __shared__ float part[4][64];
   int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   int c = blockIdx.y * 64 + lane;
@@ -44,7 +108,8 @@ __global__ __launch_bounds__(256) void colnorm_kernel(const void* __restrict__ g
     }
   part[w][lane] = s;
   __syncthreads();
-  if (w == 0 && c < D) atomicAdd(&nrm[c], (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]));
+  if (w == 0 && c < D)
+    atomicAdd(&nrm[(int64_t)(blockIdx.x % (unsigned)slots) * D + c], (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]));
 }
 
 // One group of C lanes per row (R = 64 / C rows per wave, 4 waves per
@@ -58,7 +123,7 @@ __global__ __launch_bounds__(256) void spmm_kernel(const int32_t* __restrict__ r
                                                    const int32_t* __restrict__ col,
                                                    const void* __restrict__ val, int64_t n, int D,
                                                    const void* __restrict__ g,
-                                                   const float* __restrict__ nrm_in,
+                                                   const float* __restrict__ nrm_in, int slots,
                                                    void* __restrict__ y, float* __restrict__ nrm_out) {
   constexpr int R = 64 / C;                 // rows per wave
   constexpr int U = C < 8 ? C : 8;          // gathers in flight per lane
@@ -67,10 +132,11 @@ __global__ __launch_bounds__(256) void spmm_kernel(const int32_t* __restrict__ r
   const int sub = lane / C, c = lane % C, gbase = sub * C;
   const int64_t tiles = (n + 4 * R - 1) / (4 * R);
   const int cpl = (D + C - 1) / C;          // channels per lane
+  nrm_out += (int64_t)(blockIdx.x % (unsigned)slots) * D;
   for (int k = 0; k < cpl; k += 1) {
     const int ch = c + k * C;
     const int64_t chc = ch < D ? ch : 0;
-    const float n2 = nrm_in[chc];
+    const float n2 = slot_sum<C>(nrm_in, slots, D, ch, sq);
     const float scl = n2 > 0.0f ? 1.0f / sqrtf(n2) : 0.0f;
     float ss = 0.0f;  // this lane's sum of squares of channel ch
     // Workgroups go to the 8 XCDs round-robin: XCD x (= blockIdx mod 8)
@@ -147,11 +213,11 @@ __global__ __launch_bounds__(256) void spmm1_kernel(const int32_t* __restrict__ 
                                                     const int32_t* __restrict__ col,
                                                     const void* __restrict__ val, int64_t n,
                                                     const void* __restrict__ g,
-                                                    const float* __restrict__ nrm_in,
+                                                    const float* __restrict__ nrm_in, int slots,
                                                     void* __restrict__ y, float* __restrict__ nrm_out) {
   constexpr int U = 8;
   __shared__ float sq[4];
-  const float n2 = nrm_in[0];
+  const float n2 = slot_sum<1>(nrm_in, slots, 1, 0, sq);
   const float scl = n2 > 0.0f ? 1.0f / sqrtf(n2) : 0.0f;
   float ss = 0.0f;
   // XCD x (= blockIdx mod 8) takes the x-th eighth of the rows (locality order)
@@ -188,7 +254,7 @@ __global__ __launch_bounds__(256) void spmm1_kernel(const int32_t* __restrict__ 
   __syncthreads();
   if (threadIdx.x == 0) {
     const float t = (sq[0] + sq[1]) + (sq[2] + sq[3]);
-    if (t != 0.0f) atomicAdd(&nrm_out[0], t);
+    if (t != 0.0f) atomicAdd(&nrm_out[blockIdx.x % (unsigned)slots], t);
   }
 }
 
@@ -202,16 +268,21 @@ __global__ __launch_bounds__(256) void spmm4_kernel(const int32_t* __restrict__ 
                                                     const int32_t* __restrict__ col,
                                                     const void* __restrict__ val, int64_t n,
                                                     const void* __restrict__ g,
-                                                    const float* __restrict__ nrm_in,
+                                                    const float* __restrict__ nrm_in, int slots,
                                                     void* __restrict__ y, float* __restrict__ nrm_out) {
   constexpr int D = 4 * L, R = 64 / L, U = 8;
   __shared__ float sq[256 * 4];
   const int t = threadIdx.x, lane = t & 63;
   const int sub = lane / L, c4 = lane % L, gbase = sub * L;
   float scl[4], ss[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  {
+    const float v = slot_sum<D>(nrm_in, slots, D, t & (D - 1), sq);
+    if (t < D) sq[t] = v;
+    __syncthreads();
+  }
 #pragma unroll
   for (int k = 0; k < 4; k++) {
-    const float n2 = nrm_in[4 * c4 + k];
+    const float n2 = sq[4 * c4 + k];
     scl[k] = n2 > 0.0f ? 1.0f / sqrtf(n2) : 0.0f;
   }
   const int64_t tiles = (n + 4 * R - 1) / (4 * R);
@@ -273,6 +344,7 @@ __global__ __launch_bounds__(256) void spmm4_kernel(const int32_t* __restrict__ 
       }
     }
   }
+  __syncthreads();  // the norms in sq are read
   // per-channel sums over the block: threads t = c4 (mod L) hold channels 4 c4 .. 4 c4 + 3
 #pragma unroll
   for (int k = 0; k < 4; k++) sq[k * 256 + t] = ss[k];
@@ -281,7 +353,7 @@ __global__ __launch_bounds__(256) void spmm4_kernel(const int32_t* __restrict__ 
     const int k = t & 3, cc = t >> 2;
     float s2 = 0.0f;
     for (int q = cc; q < 256; q += L) s2 += sq[k * 256 + q];
-    if (s2 != 0.0f) atomicAdd(&nrm_out[t], s2);
+    if (s2 != 0.0f) atomicAdd(&nrm_out[(int64_t)(blockIdx.x % (unsigned)slots) * D + t], s2);
   }
 }
 
@@ -293,7 +365,7 @@ __global__ void copy_kernel(const void* __restrict__ src, void* __restrict__ dst
 
 template <int C, lv_dtype GT, lv_dtype VT>
 hipError_t spmm_launch(const int32_t* rp, const int32_t* col, const void* val, int64_t n, int D,
-                       const void* g, const float* nin, void* y, float* nout, hipStream_t s) {
+                       const void* g, const float* nin, int slots, void* y, float* nout, hipStream_t s) {
   constexpr int R = 64 / C;
   const int64_t rows_per_tile = 4 * R;
   const int64_t tiles = (n + rows_per_tile - 1) / rows_per_tile;
@@ -302,46 +374,48 @@ hipError_t spmm_launch(const int32_t* rp, const int32_t* col, const void* val, i
   const int64_t want = (tiles + 7) / 8 * 8;
   const unsigned blocks = (unsigned)(want < 8192 ? want : 8192);
   hipLaunchKernelGGL((spmm_kernel<C, GT, VT>), dim3(blocks), dim3(256), 0, s, rp, col, val, n, D, g,
-                     nin, y, nout);
+                     nin, slots, y, nout);
   return hipGetLastError();
 }
 
 template <int L, lv_dtype GT, lv_dtype VT>
 hipError_t spmm4_launch(const int32_t* rp, const int32_t* col, const void* val, int64_t n,
-                        const void* g, const float* nin, void* y, float* nout, hipStream_t s) {
+                        const void* g, const float* nin, int slots, void* y, float* nout,
+                        hipStream_t s) {
   constexpr int R = 64 / L;
   const int64_t tiles = (n + 4 * R - 1) / (4 * R);
   const int64_t want = (tiles + 7) / 8 * 8;
   const unsigned blocks = (unsigned)(want < 8192 ? want : 8192);
   hipLaunchKernelGGL((spmm4_kernel<L, GT, VT>), dim3(blocks), dim3(256), 0, s, rp, col, val, n, g, nin,
-                     y, nout);
+                     slots, y, nout);
   return hipGetLastError();
 }
 
 template <lv_dtype GT, lv_dtype VT>
 hipError_t spmm_dispatch(const int32_t* rp, const int32_t* col, const void* val, int64_t n, int D,
-                         const void* g, const float* nin, void* y, float* nout, hipStream_t s) {
+                         const void* g, const float* nin, int slots, void* y, float* nout,
+                         hipStream_t s) {
   if (D == 1) {
     const int64_t tiles = (n + 255) / 256;
     const int64_t want = (tiles + 7) / 8 * 8;
     const unsigned blocks = (unsigned)(want < 8192 ? want : 8192);
-    hipLaunchKernelGGL((spmm1_kernel<GT, VT>), dim3(blocks), dim3(256), 0, s, rp, col, val, n, g, nin, y,
-                       nout);
+    hipLaunchKernelGGL((spmm1_kernel<GT, VT>), dim3(blocks), dim3(256), 0, s, rp, col, val, n, g, nin,
+                       slots, y, nout);
     return hipGetLastError();
   }
   // four channels per lane where D = 4 L, L a power of two up to 16 and the
   // rows are 16-byte (FP32) or 8-byte (BF16) aligned
   if (((uintptr_t)g % 16 == 0) && ((uintptr_t)y % 16 == 0)) {
-    if (D == 64) return spmm4_launch<16, GT, VT>(rp, col, val, n, g, nin, y, nout, s);
-    if (D == 32) return spmm4_launch<8, GT, VT>(rp, col, val, n, g, nin, y, nout, s);
-    if (D == 16) return spmm4_launch<4, GT, VT>(rp, col, val, n, g, nin, y, nout, s);
-    if (D == 8) return spmm4_launch<2, GT, VT>(rp, col, val, n, g, nin, y, nout, s);
-    if (D == 4) return spmm4_launch<1, GT, VT>(rp, col, val, n, g, nin, y, nout, s);
+    if (D == 64) return spmm4_launch<16, GT, VT>(rp, col, val, n, g, nin, slots, y, nout, s);
+    if (D == 32) return spmm4_launch<8, GT, VT>(rp, col, val, n, g, nin, slots, y, nout, s);
+    if (D == 16) return spmm4_launch<4, GT, VT>(rp, col, val, n, g, nin, slots, y, nout, s);
+    if (D == 8) return spmm4_launch<2, GT, VT>(rp, col, val, n, g, nin, slots, y, nout, s);
+    if (D == 4) return spmm4_launch<1, GT, VT>(rp, col, val, n, g, nin, slots, y, nout, s);
   }
-  if (D >= 64) return spmm_launch<64, GT, VT>(rp, col, val, n, D, g, nin, y, nout, s);
-  if (D > 16) return spmm_launch<32, GT, VT>(rp, col, val, n, D, g, nin, y, nout, s);
-  if (D > 4) return spmm_launch<8, GT, VT>(rp, col, val, n, D, g, nin, y, nout, s);
-  return spmm_launch<1, GT, VT>(rp, col, val, n, D, g, nin, y, nout, s);
+  if (D >= 64) return spmm_launch<64, GT, VT>(rp, col, val, n, D, g, nin, slots, y, nout, s);
+  if (D > 16) return spmm_launch<32, GT, VT>(rp, col, val, n, D, g, nin, slots, y, nout, s);
+  if (D > 4) return spmm_launch<8, GT, VT>(rp, col, val, n, D, g, nin, slots, y, nout, s);
+  return spmm_launch<1, GT, VT>(rp, col, val, n, D, g, nin, slots, y, nout, s);
 }
 
 template <lv_dtype GT>
@@ -355,19 +429,27 @@ hipError_t diffuse_t(const int32_t* rp, const int32_t* col, const void* val, lv_
                        out, total);
     return hipGetLastError();
   }
-  hipError_t e = hipMemsetAsync(norms, 0, sizeof(float) * (size_t)D * (size_t)(steps + 1), s);
+  const int slots = norm_slots(D);
+  const size_t row = (size_t)D * slots;  // the norms of one step
+  hipError_t e = hipMemsetAsync(norms, 0, sizeof(float) * row * (size_t)(steps + 1), s);
   if (e != hipSuccess) return e;
   if (total == 0) return hipSuccess;
-  int rows = 256;
-  hipLaunchKernelGGL(colnorm_kernel<GT>, dim3((unsigned)((n + rows - 1) / rows), (D + 63) / 64),
-                     dim3(256), 0, s, g0, n, D, rows, norms);
+  if (D <= 64) {
+    const int64_t want = (n + 256 / D - 1) / (256 / D);
+    hipLaunchKernelGGL(colnorm_flat_kernel<GT>, dim3((unsigned)(want < 1024 ? want : 1024)), dim3(256), 0,
+                       s, g0, n, D, slots, norms);
+  } else {
+    const int rows = 256;
+    hipLaunchKernelGGL(colnorm_kernel<GT>, dim3((unsigned)((n + rows - 1) / rows), (D + 63) / 64),
+                       dim3(256), 0, s, g0, n, D, rows, slots, norms);
+  }
   const void* cur = g0;
   for (int t = 0; t < steps; t++) {
     void* dst = (t == steps - 1) ? out : ((t & 1) ? b1 : b0);
-    e = vt == LV_F32 ? spmm_dispatch<GT, LV_F32>(rp, col, val, n, D, cur, norms + (size_t)t * D, dst,
-                                                 norms + (size_t)(t + 1) * D, s)
-                     : spmm_dispatch<GT, LV_BF16>(rp, col, val, n, D, cur, norms + (size_t)t * D, dst,
-                                                  norms + (size_t)(t + 1) * D, s);
+    e = vt == LV_F32 ? spmm_dispatch<GT, LV_F32>(rp, col, val, n, D, cur, norms + t * row, slots, dst,
+                                                 norms + (t + 1) * row, s)
+                     : spmm_dispatch<GT, LV_BF16>(rp, col, val, n, D, cur, norms + t * row, slots, dst,
+                                                  norms + (t + 1) * row, s);
     if (e != hipSuccess) return e;
     cur = dst;
   }
@@ -521,6 +603,8 @@ __global__ void permute_rows_kernel(const T* __restrict__ src, T* __restrict__ d
 }
 
 }  // namespace
+
+size_t diffuse_norm_floats(int D, int steps) { return (size_t)D * norm_slots(D) * (size_t)(steps + 1); }
 
 hipError_t launch_diffuse(const int32_t* row_ptr, const int32_t* col, const void* val,
                           lv_dtype val_dtype, int64_t n, const void* g0, lv_dtype dtype, int D,

@@ -328,6 +328,8 @@ lv_status run_batch(lv_scene* sc, const lv_camera* cams, int32_t m, const BatchS
 // returns st.
 lv_status set_error(lv_status st, const char* fmt, ...);
 
+// Floats of `norms` for launch_diffuse.
+size_t diffuse_norm_floats(int D, int steps);
 hipError_t launch_diffuse(const int32_t* row_ptr, const int32_t* col, const void* val,
                           lv_dtype val_dtype, int64_t n, const void* g0, lv_dtype dtype, int D,
                           int steps, void* out, float* buf0, float* buf1, float* norms,
