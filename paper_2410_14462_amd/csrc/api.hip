@@ -116,6 +116,7 @@ struct Workspace {
   const uint32_t* dval = nullptr;
   Buf rec, key0, val0, key1, val1, rect, scnt, srect, off, scan_tmp, hist, seg, pseg, total;
   Buf pk0, pv0, pk1, pv1, hist2, ranges, cams, geom, maps;
+  Buf graph;  // graph builds and orders
   Buf cls;  // beta and count increments of classes of sets taking the same views
   HostBuf up, down;
 };
@@ -142,7 +143,7 @@ void workspace_free(Workspace* w, hipStream_t s) {
     Buf* bufs[] = {&w->rec, &w->key0, &w->val0, &w->key1, &w->val1, &w->rect, &w->scnt,
                    &w->srect, &w->off, &w->scan_tmp, &w->hist, &w->seg, &w->pseg, &w->total,
                    &w->pk0, &w->pv0, &w->pk1, &w->pv1, &w->hist2, &w->ranges, &w->cams,
-                   &w->geom, &w->maps, &w->cls};
+                   &w->geom, &w->maps, &w->graph, &w->cls};
     for (Buf* b : bufs) b->release(s);
     w->up.release();
     w->down.release();
@@ -216,6 +217,7 @@ struct lv_accum {
 
 struct lv_graph {
   int64_t n = 0, nnz = 0;
+  int device = 0;
   lv_dtype val_dtype = LV_F32;
   Buf row_ptr, col, val, b0, b1, norms;
   // locality order (built on the first call that passes a scene)
@@ -591,13 +593,14 @@ lv_status lv_memory_stats(int64_t* bytes, int64_t* allocations) {
 const char* lv_version(void) { return "lv 0.1 gfx950"; }
 
 namespace {
-// Device buffers of destroyed scenes, kept for the next scenes of a similar
-// size (a scene that is created and destroyed per request then costs no
-// allocation); bounded in count and bytes, buffers above kSceneCacheMaxBuf
-// are freed at once.
+// Device buffers of destroyed scenes and graphs, kept for the next ones of a
+// similar size (a scene that is created and destroyed per request then costs
+// no allocation, nor a graph that is built per result: hipMalloc and hipFree of
+// its arrays took 2.4 ms of a 1M-node build); bounded in count and bytes,
+// buffers above kSceneCacheMaxBuf are freed at once.
 std::mutex g_scene_cache_mu;
 std::vector<std::pair<int, Buf>> g_scene_cache;
-constexpr size_t kSceneCacheBufs = 12;
+constexpr size_t kSceneCacheBufs = 24;
 constexpr size_t kSceneCacheMaxBuf = (size_t)256 << 20;
 constexpr size_t kSceneCacheBytes = (size_t)1 << 30;
 
@@ -1297,9 +1300,10 @@ lv_status lv_graph_create_csr(int64_t n, int64_t nnz, const int32_t* row_ptr, co
   g->n = n;
   g->nnz = nnz;
   g->val_dtype = val_dtype;
-  hipError_t e = g->row_ptr.ensure(4 * (size_t)(n + 1), s);
-  if (e == hipSuccess) e = g->col.ensure(4 * (size_t)(nnz + 1), s);
-  if (e == hipSuccess) e = g->val.ensure(dtype_size(val_dtype) * (size_t)(nnz + 1), s);
+  (void)hipGetDevice(&g->device);
+  hipError_t e = scene_buf(g->row_ptr, g->device, 4 * (size_t)(n + 1), s);
+  if (e == hipSuccess) e = scene_buf(g->col, g->device, 4 * (size_t)(nnz + 1), s);
+  if (e == hipSuccess) e = scene_buf(g->val, g->device, dtype_size(val_dtype) * (size_t)(nnz + 1), s);
   if (e == hipSuccess) e = hipMemcpyAsync(g->row_ptr.p, row_ptr, 4 * (size_t)(n + 1), hipMemcpyDeviceToDevice, s);
   if (e == hipSuccess && nnz) e = hipMemcpyAsync(g->col.p, col, 4 * (size_t)nnz, hipMemcpyDeviceToDevice, s);
   if (e == hipSuccess && nnz)
@@ -1339,24 +1343,39 @@ lv_status lv_graph_build_knn(lv_scene* sc, const float* feats, int32_t D, int32_
     }
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
+  lv_graph* g = new (std::nothrow) lv_graph();
+  if (!g) return fail(LV_ERR_OUT_OF_MEMORY, "host allocation");
+  (void)hipGetDevice(&g->device);
   int32_t *rp = nullptr, *cl = nullptr;
   float* vl = nullptr;
-  int64_t nnz = 0;
-  HIP_TRY(build_knn_graph(sc->caller_p0(), n, feats, D, k, gw, s, &rp, &cl, &vl, &nnz));
-  lv_graph* g = new (std::nothrow) lv_graph();
-  if (!g) {
-    (void)hipStreamSynchronize(s);
-    dev_free(rp, 4 * (size_t)(n + 1), s);
-    dev_free(cl, 4 * (size_t)(nnz + 1), s);
-    dev_free(vl, 4 * (size_t)(nnz + 1), s);
-    return fail(LV_ERR_OUT_OF_MEMORY, "host allocation");
+  hipError_t e;
+  {
+    Workspace& ws = *workspace_for(s);
+    std::lock_guard<std::mutex> lk(ws.mu);
+    GraphAlloc alloc;
+    alloc.scratch = [&](void** p, size_t bytes) {
+      const hipError_t r = ws.graph.ensure(bytes, s);
+      *p = ws.graph.p;
+      return r;
+    };
+    alloc.csr = [&](int64_t nnz, int32_t** r, int32_t** c, float** v) {
+      hipError_t q = scene_buf(g->row_ptr, g->device, 4 * (size_t)(n + 1), s);
+      if (q == hipSuccess) q = scene_buf(g->col, g->device, 4 * (size_t)(nnz + 1), s);
+      if (q == hipSuccess) q = scene_buf(g->val, g->device, 4 * (size_t)(nnz + 1), s);
+      *r = g->row_ptr.as<int32_t>();
+      *c = g->col.as<int32_t>();
+      *v = g->val.as<float>();
+      return q;
+    };
+    e = build_knn_graph(sc->caller_p0(), n, feats, D, k, gw, s, alloc, &rp, &cl, &vl, &g->nnz);
+  }
+  if (e != hipSuccess) {  // the stream is synchronised
+    g->row_ptr.release(); g->col.release(); g->val.release();
+    delete g;
+    HIP_TRY(e);
   }
   g->n = n;
-  g->nnz = nnz;
   g->val_dtype = LV_F32;
-  g->row_ptr.p = rp; g->row_ptr.cap = 4 * (size_t)(n + 1);
-  g->col.p = cl; g->col.cap = 4 * (size_t)(nnz + 1);
-  g->val.p = vl; g->val.cap = 4 * (size_t)(nnz + 1);
   *out = g;
   return LV_OK;
 }
@@ -1377,10 +1396,9 @@ lv_status lv_graph_csr(const lv_graph* g, int64_t* n, int64_t* nnz, int32_t* row
 lv_status lv_graph_destroy(lv_graph* g) {
   if (!g) return LV_OK;
   (void)hipDeviceSynchronize();
-  g->row_ptr.release(); g->col.release(); g->val.release();
-  g->b0.release(); g->b1.release(); g->norms.release();
-  g->perm.release(); g->inv.release(); g->rp2.release(); g->col2.release(); g->val2.release();
-  g->bin.release(); g->bout.release();
+  Buf* bufs[] = {&g->row_ptr, &g->col, &g->val, &g->b0, &g->b1, &g->norms, &g->perm,
+                 &g->inv, &g->rp2, &g->col2, &g->val2, &g->bin, &g->bout};
+  for (Buf* b : bufs) scene_buf_release(g->device, *b);
   if (g->last) (void)hipEventDestroy(g->last);
   delete g;
   return LV_OK;
@@ -1402,33 +1420,35 @@ lv_status lv_diffuse(const lv_scene* sc, const lv_graph* gc, const void* g0, lv_
   else HIP_TRY(hipEventCreateWithFlags(&g->last, hipEventDisableTiming));
   const bool order = sc && g->n > 0 && steps > 0;
   const size_t sig = dtype_size(dtype) * (size_t)(g->n > 0 ? g->n : 1) * D;
-  HIP_TRY(g->b0.ensure(sig, s));
-  HIP_TRY(g->b1.ensure(sig, s));
-  HIP_TRY(g->norms.ensure(sizeof(float) * diffuse_norm_floats(D, steps), s));
+  const auto grow = [&](Buf& b, size_t bytes) {  // a first buffer from the cache
+    return b.p ? b.ensure(bytes, s) : scene_buf(b, g->device, bytes, s);
+  };
+  HIP_TRY(grow(g->b0, sig));
+  HIP_TRY(grow(g->b1, sig));
+  HIP_TRY(grow(g->norms, sizeof(float) * diffuse_norm_floats(D, steps)));
   if (order && !g->ordered) {
     // P A P^T along the Morton order of the scene's centres; any permutation
     // gives the same result, so the order is built once per graph.
     const int64_t n = g->n, nnz = g->nnz;
-    Buf scratch;
-    HIP_TRY(scratch.ensure(4 * reorder_scratch_words(n), s));
-    hipError_t e = g->perm.ensure(4 * (size_t)n, s);
-    if (e == hipSuccess) e = g->inv.ensure(4 * (size_t)n, s);
-    if (e == hipSuccess) e = g->rp2.ensure(4 * (size_t)(n + 1), s);
-    if (e == hipSuccess) e = g->col2.ensure(4 * (size_t)(nnz + 1), s);
-    if (e == hipSuccess) e = g->val2.ensure(dtype_size(g->val_dtype) * (size_t)(nnz + 1), s);
+    Workspace& ws = *workspace_for(s);
+    std::lock_guard<std::mutex> wlk(ws.mu);
+    HIP_TRY(ws.graph.ensure(4 * reorder_scratch_words(n), s));
+    hipError_t e = grow(g->perm, 4 * (size_t)n);
+    if (e == hipSuccess) e = grow(g->inv, 4 * (size_t)n);
+    if (e == hipSuccess) e = grow(g->rp2, 4 * (size_t)(n + 1));
+    if (e == hipSuccess) e = grow(g->col2, 4 * (size_t)(nnz + 1));
+    if (e == hipSuccess) e = grow(g->val2, dtype_size(g->val_dtype) * (size_t)(nnz + 1));
     if (e == hipSuccess)
       e = launch_graph_reorder(sc->caller_p0(), n, g->row_ptr.as<int32_t>(), g->col.as<int32_t>(),
-                               g->val.p, g->val_dtype, nnz, scratch.as<uint32_t>(),
+                               g->val.p, g->val_dtype, nnz, ws.graph.as<uint32_t>(),
                                g->perm.as<uint32_t>(), g->inv.as<uint32_t>(), g->rp2.as<int32_t>(),
                                g->col2.as<int32_t>(), g->val2.p, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    scratch.release();
     if (e != hipSuccess) return fail(LV_ERR_DEVICE, "graph order: %s", hipGetErrorString(e));
     g->ordered = true;
   }
   if (order) {
-    HIP_TRY(g->bin.ensure(sig, s));
-    HIP_TRY(g->bout.ensure(sig, s));
+    HIP_TRY(grow(g->bin, sig));
+    HIP_TRY(grow(g->bout, sig));
     const uint32_t* perm = g->perm.as<uint32_t>();
     HIP_TRY(launch_permute_rows(g0, g->bin.p, perm, g->n, D, dtype, false, s));
     HIP_TRY(launch_diffuse(g->rp2.as<int32_t>(), g->col2.as<int32_t>(), g->val2.p, g->val_dtype, g->n,

@@ -7,6 +7,8 @@
 #include <rocprofiler-sdk-roctx/roctx.h>
 #include <stdint.h>
 
+#include <functional>
+
 #include "lv.h"
 
 namespace lv {
@@ -276,9 +278,13 @@ hipError_t launch_render(const BlendArgs& a, int m, const float* g, int D, float
 // allocator).
 hipError_t launch_prune(const float* wsum, int64_t n, int64_t k, uint8_t* keep, hipStream_t s);
 // kNN diffusion graph over the centres (xyz of centres[i]) with feature
-// weights (feats [n][D]); CSR arrays allocated with hipMalloc (owned by the
-// caller afterwards); synchronises the stream once (to size the CSR).
-// Requires k < n, 1 <= k <= 32, n (2k + 1) < 2^31.
+// weights (feats [n][D]); scratch and CSR arrays through `alloc` (the arrays
+// are the caller's, also on an error); synchronises the stream once (to size
+// the CSR).  Requires k < n, 1 <= k <= 32, n (2k + 1) < 2^31.
+struct GraphAlloc {
+  std::function<hipError_t(void** p, size_t bytes)> scratch;  // valid until the stream's work ends
+  std::function<hipError_t(int64_t nnz, int32_t** row_ptr, int32_t** col, float** val)> csr;
+};
 struct GraphWeights {
   int32_t kind = LV_GRAPH_SPATIAL_COSINE;
   float bandwidth = 1.0f;        // b (feature kernel)
@@ -286,8 +292,8 @@ struct GraphWeights {
   float binarize = 0.0f;         // > 0 (feature kernel): 1 where the weight exceeds it
 };
 hipError_t build_knn_graph(const float4* centres, int64_t n, const float* feats, int D, int k,
-                           const GraphWeights& gw, hipStream_t s, int32_t** row_ptr, int32_t** col,
-                           float** val, int64_t* nnz);
+                           const GraphWeights& gw, hipStream_t s, const GraphAlloc& alloc,
+                           int32_t** row_ptr, int32_t** col, float** val, int64_t* nnz);
 // g0 = g on the ceil(fraction npos) largest positive entries (ties to the
 // lower index), 0 elsewhere.
 hipError_t launch_anchor_init(const float* g, int64_t n, float fraction, float* g0, hipStream_t s);
