@@ -1512,7 +1512,9 @@ lv_status lv_render(lv_scene* sc, const lv_camera* cams, int32_t m, const float*
     HIP_TRY(ws.maps.ensure(bytes, s));
     HIP_TRY(ws.up.ensure(bytes));
     float** up = static_cast<float**>(ws.up.p);
+    uintptr_t outs_align = 0;
     for (int v = 0; v < mv; v++) {
+      outs_align |= (uintptr_t)outs[v0 + v];
       up[v] = outs[v0 + v];
       up[mv + v] = alphas ? alphas[v0 + v] : nullptr;
     }
@@ -1526,7 +1528,7 @@ lv_status lv_render(lv_scene* sc, const lv_camera* cams, int32_t m, const float*
     ba.n = n;
     ba.tiles_stride = stride;
     float* const* dtab = static_cast<float* const*>(ws.maps.p);
-    st = profiled_launch(s, [&] { return launch_render(ba, mv, g, D, dtab, dtab + mv, perm, s); });
+    st = profiled_launch(s, [&] { return launch_render(ba, mv, g, D, dtab, outs_align, dtab + mv, perm, s); });
     if (st != LV_OK) return st;
     v0 += mv;
   }

@@ -1112,8 +1112,12 @@ hipError_t launch_blend_t(const BlendArgs& a, int m, hipStream_t s) {
 // for D <= 64, else 4: the walk, repeated for every group of channels, runs
 // half as often, and the 8 output blocks' 128 registers leave 2 waves per
 // SIMD instead of 3.
-template <int NB>
-__global__ __launch_bounds__(64, (NB == 2 ? 3 : 2)) void render_kernel(
+// kVec: D is a multiple of NB and g and the outputs are aligned to NB floats;
+// a lane's channels are then consecutive (channel NB (l % 32) + b in block b),
+// and each row of g and each output pixel is one load or store of NB floats
+// instead of NB.  Else block b's channels are 32 b + l % 32.
+template <int NB, bool kVec>
+__global__ __launch_bounds__(64, (NB == 1 ? 4 : NB == 2 ? 3 : 2)) void render_kernel(
     const Rec* __restrict__ rec, const uint32_t* __restrict__ ids, const uint2* __restrict__ ranges,
     const ViewGeom* __restrict__ geom, int64_t n, int tiles_stride, int nviews, int ngroups,
     const float* __restrict__ g, int D, float* const* __restrict__ outs,
@@ -1133,10 +1137,11 @@ __global__ __launch_bounds__(64, (NB == 2 ? 3 : 2)) void render_kernel(
   bool own[NB];
 #pragma unroll
   for (int b = 0; b < NB; b++) {
-    ch[b] = c0 + 32 * b + (lane & 31);
+    ch[b] = kVec ? c0 + NB * (lane & 31) + b : c0 + 32 * b + (lane & 31);
     own[b] = ch[b] < D;
-    if (!own[b]) ch[b] = 0;
+    if (!own[b]) ch[b] = kVec ? b : 0;
   }
+  typedef float fvec __attribute__((ext_vector_type(NB)));
   f32x16 acc[2][NB];  // [pixel block][channel block]
 #pragma unroll
   for (int b = 0; b < NB; b++) acc[0][b] = acc[1][b] = f32x16{};
@@ -1162,10 +1167,20 @@ __global__ __launch_bounds__(64, (NB == 2 ? 3 : 2)) void render_kernel(
         w1[i] = ok ? Wt[row * kWtPitch + 32 + (lane & 31)] : 0.0f;
       }
       float gb[NB][8];
+      if constexpr (kVec && NB > 1) {
+        fvec r[8];
 #pragma unroll
-      for (int c = 0; c < NB; c++)
+        for (int i = 0; i < 8; i++) r[i] = *reinterpret_cast<const fvec*>(g + gid[i] * D + ch[0]);
 #pragma unroll
-        for (int i = 0; i < 8; i++) gb[c][i] = g[gid[i] * D + ch[c]];
+        for (int i = 0; i < 8; i++)
+#pragma unroll
+          for (int c = 0; c < NB; c++) gb[c][i] = r[i][c];
+      } else {
+#pragma unroll
+        for (int c = 0; c < NB; c++)
+#pragma unroll
+          for (int i = 0; i < 8; i++) gb[c][i] = g[gid[i] * D + ch[c]];
+      }
       bf16x8 a0h, a0l, a1h, a1l;
       split8(w0, a0h, a0l);
       split8(w1, a1h, a1l);
@@ -1222,9 +1237,16 @@ __global__ __launch_bounds__(64, (NB == 2 ? 3 : 2)) void render_kernel(
       const int px = q.qx + (m & 7), py = q.qy + (m >> 3);
       if (px < q.g.W && py < q.g.H) {
         const int64_t pix = (int64_t)py * q.g.W + px;
+        if constexpr (kVec && NB > 1) {
+          fvec o;
 #pragma unroll
-        for (int c = 0; c < NB; c++)
-          if (own[c]) gptr(out)[pix * D + ch[c]] = acc[pb][c][r];
+          for (int c = 0; c < NB; c++) o[c] = acc[pb][c][r];
+          if (own[0]) *gptr(reinterpret_cast<fvec*>(out + pix * D + ch[0])) = o;
+        } else {
+#pragma unroll
+          for (int c = 0; c < NB; c++)
+            if (own[c]) gptr(out)[pix * D + ch[c]] = acc[pb][c][r];
+        }
       }
     }
   }
@@ -1328,18 +1350,18 @@ hipError_t launch_blend(const BlendArgs& a, lv_dtype dtype, int m, hipStream_t s
 }
 
 hipError_t launch_render(const BlendArgs& a, int m, const float* g, int D, float* const* outs,
-                         float* const* alphas, const uint32_t* perm, hipStream_t s) {
+                         uintptr_t outs_align, float* const* alphas, const uint32_t* perm, hipStream_t s) {
   if (m == 0 || a.tiles_stride == 0) return hipSuccess;
-  const int ch = D > 64 ? 128 : 64;  // channels per wave
-  const int ngroups = (D + ch - 1) / ch;
+  const int nb = D > 64 ? 4 : D > 32 ? 2 : 1;  // 32-channel blocks per wave
+  const int ngroups = (D + 32 * nb - 1) / (32 * nb);
   const int64_t work = (int64_t)a.tiles_stride * m * ngroups;
   const int64_t blocks = (work + 7) / 8 * 32;  // 4 quadrants per tile, whole rounds of 8 XCDs
-  if (ch == 128)
-    hipLaunchKernelGGL(render_kernel<4>, dim3((unsigned)blocks), dim3(64), 0, s, a.rec, a.ids,
-                       a.ranges, a.geom, a.n, a.tiles_stride, m, ngroups, g, D, outs, alphas, perm);
-  else
-    hipLaunchKernelGGL(render_kernel<2>, dim3((unsigned)blocks), dim3(64), 0, s, a.rec, a.ids,
-                       a.ranges, a.geom, a.n, a.tiles_stride, m, ngroups, g, D, outs, alphas, perm);
+  const bool vec = D % nb == 0 && (uintptr_t)g % (4 * nb) == 0 && outs_align % (4 * nb) == 0;
+  const auto kernel = nb == 1   ? render_kernel<1, false>
+                      : nb == 2 ? (vec ? render_kernel<2, true> : render_kernel<2, false>)
+                                : (vec ? render_kernel<4, true> : render_kernel<4, false>);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64), 0, s, a.rec, a.ids, a.ranges, a.geom, a.n,
+                     a.tiles_stride, m, ngroups, g, D, outs, alphas, perm);
   return hipGetLastError();
 }
 

@@ -270,9 +270,9 @@ hipError_t launch_class_add(const beta_t* beta, const uint32_t* counts, const Cl
 // m pointers) and the accumulated opacity into alphas[v] [H][W] (entries may
 // be null); every in-image pixel is written (zeros where no Gaussian
 // reaches).  perm (nullable): storage -> caller order of the scene; g is in
-// the caller's order.
+// the caller's order.  outs_align: the bitwise or of the output addresses.
 hipError_t launch_render(const BlendArgs& a, int m, const float* g, int D, float* const* outs,
-                         float* const* alphas, const uint32_t* perm, hipStream_t s);
+                         uintptr_t outs_align, float* const* alphas, const uint32_t* perm, hipStream_t s);
 // Keep the k Gaussians with the largest wsum (ties to the lower index):
 // keep[i] = 1 for them, 0 for the others (scratch from the stream-ordered
 // allocator).
