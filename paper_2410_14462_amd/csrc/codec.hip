@@ -39,6 +39,35 @@ __device__ __forceinline__ uint8_t to_e4m3(float x) {
   return (uint8_t)(sign | code);
 }
 
+// E4M3 codes of two floats (low byte: x) by the hardware conversion (round to
+// nearest even, subnormals kept); what is not below 448 saturates first, as in
+// to_e4m3, so that neither its overflow nor its NaN code is ever made.
+__device__ __forceinline__ uint32_t e4m3x2(float x, float y) {
+  x = fabsf(x) < 448.0f ? x : copysignf(448.0f, x);
+  y = fabsf(y) < 448.0f ? y : copysignf(448.0f, y);
+  return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(x, y, 0, false) & 0xFFFFu;
+}
+
+// x / sc, correctly rounded as by the division, for many x and one sc: with rc
+// the correctly rounded reciprocal, q = x rc is within an ulp, r = x - q sc is
+// exact in one fused operation, and q + r rc rounds to the quotient (Markstein,
+// IBM J. Res. Dev. 34(1), 1990) unless sc's significand is all ones.  rc = 0
+// asks for the division itself: that significand, and scales so small or large
+// that r, or the products, would leave the normal range for an x whose code is
+// not zero.
+struct ChanScale {
+  float sc, rc;
+  __device__ __forceinline__ void set(float amax) {
+    sc = amax > 0.0f ? amax / 448.0f : 1.0f;
+    const bool plain = sc > 0x1p-80f && sc < 0x1p80f && (__float_as_uint(sc) & 0x7FFFFFu) != 0x7FFFFFu;
+    rc = plain ? 1.0f / sc : 0.0f;
+  }
+  __device__ __forceinline__ float div(float x) const {
+    const float q = x * rc;
+    return copysignf(__builtin_fmaf(__builtin_fmaf(-q, sc, x), rc, q), x);  // -0 stays -0
+  }
+};
+
 // Elements [first, total), one per thread.
 __global__ void encode_bf16_kernel(const float* __restrict__ src, int64_t first, int64_t total,
                                    uint16_t* __restrict__ dst) {
@@ -83,6 +112,49 @@ __global__ __launch_bounds__(256) void absmax_kernel(const float* __restrict__ s
   }
 }
 
+// Per-channel absmax for D a multiple of 4 and a 16-byte aligned map: the map
+// as one run of float4, a grid stride that is a multiple of D / 4, so that a
+// thread keeps its four channels; maxima meet in LDS, one atomic per channel
+// and block.  A pass over the map is bound by its reads (one channel per lane,
+// 4-byte loads: 360 us for 1.17 GB; now 197, 5.9 TB/s).
+__global__ __launch_bounds__(1024) void absmax4_kernel(const float4* __restrict__ src, int64_t total4, int Q,
+                                                       uint32_t* __restrict__ amax) {
+  extern __shared__ uint32_t smax[];
+  const int64_t threads = (int64_t)gridDim.x * 1024, step = threads - threads % Q;
+  const int64_t first = (int64_t)blockIdx.x * 1024 + threadIdx.x;
+  for (int e = threadIdx.x; e < 4 * Q; e += 1024) smax[e] = 0u;
+  __syncthreads();
+  if (first < step && first < total4) {
+    float m[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    int64_t i = first;
+    for (; i + 3 * step < total4; i += 4 * step) {
+      float4 a[4];
+#pragma unroll
+      for (int u = 0; u < 4; u++) a[u] = src[i + u * step];
+#pragma unroll
+      for (int u = 0; u < 4; u++) {
+        m[0] = fmaxf(m[0], fabsf(a[u].x));
+        m[1] = fmaxf(m[1], fabsf(a[u].y));
+        m[2] = fmaxf(m[2], fabsf(a[u].z));
+        m[3] = fmaxf(m[3], fabsf(a[u].w));
+      }
+    }
+    for (; i < total4; i += step) {
+      const float4 a = src[i];
+      m[0] = fmaxf(m[0], fabsf(a.x));
+      m[1] = fmaxf(m[1], fabsf(a.y));
+      m[2] = fmaxf(m[2], fabsf(a.z));
+      m[3] = fmaxf(m[3], fabsf(a.w));
+    }
+    const int c = 4 * (int)(first % Q);
+#pragma unroll
+    for (int k = 0; k < 4; k++) atomicMax(&smax[c + k], __float_as_uint(m[k]));
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < 4 * Q; e += 1024)
+    if (smax[e]) atomicMax(&amax[e], smax[e]);
+}
+
 __global__ void zero_kernel(uint32_t* __restrict__ p, int n) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0u;
@@ -122,6 +194,101 @@ __global__ __launch_bounds__(256) void encode_fp8_vec_kernel(const float4* __res
       else hi |= q << (8 * (j - 4));
     }
     dst[k] = make_uint2(lo, hi);
+  }
+}
+
+// HWC for D a multiple of 4, aligned: a thread keeps its four channels (as
+// absmax4_kernel), four codes per store.  The last elements first: those the
+// absmax pass read last are still in the memory-side cache.
+__global__ __launch_bounds__(256) void encode_fp8_quad_kernel(const float4* __restrict__ src, int64_t total4,
+                                                              int Q, const uint32_t* __restrict__ amax,
+                                                              float* __restrict__ scales,
+                                                              uint32_t* __restrict__ dst) {
+  const int64_t threads = (int64_t)gridDim.x * 256, step = threads - threads % Q;
+  const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (first >= step || first >= total4) return;
+  const int c = 4 * (int)(first % Q);
+  ChanScale cs[4];
+#pragma unroll
+  for (int k = 0; k < 4; k++) cs[k].set(__uint_as_float(amax[c + k]));
+  const bool plain = cs[0].rc != 0.0f && cs[1].rc != 0.0f && cs[2].rc != 0.0f && cs[3].rc != 0.0f;
+  if (first < Q)
+#pragma unroll
+    for (int k = 0; k < 4; k++) scales[c + k] = cs[k].sc;
+#pragma unroll 4
+  for (int64_t i = first + (total4 - 1 - first) / step * step; i >= 0; i -= step) {
+    const float4 a = src[i];
+    float v[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+    for (int k = 0; k < 4; k++) v[k] = plain ? cs[k].div(v[k]) : v[k] / cs[k].sc;
+    dst[i] = e4m3x2(v[0], v[1]) | (e4m3x2(v[2], v[3]) << 16);
+  }
+}
+
+// Pixel-block layout for D a multiple of 4, aligned: a thread takes four
+// channels of a block of 8 pixels (eight 16-byte loads, consecutive threads on
+// consecutive channels), the last blocks first.  1008x756x384 in FP8: 347 us
+// one channel per thread with the IEEE division and the conversion in software
+// (about 30 vector operations an element), 253 now.
+template <lv_dtype E>
+__global__ __launch_bounds__(256) void encode_px8_quad_kernel(const float4* __restrict__ src, int W, int Q,
+                                                              uint32_t runs4, const uint32_t* __restrict__ amax,
+                                                              float* __restrict__ scales,
+                                                              void* __restrict__ dst) {
+  const uint32_t W8 = (uint32_t)(W + 7) >> 3;
+  const uint32_t r = blockIdx.x * 256u + threadIdx.x;
+  if (r >= runs4) return;
+  const uint32_t k = runs4 - 1u - r, blk = k / (uint32_t)Q, q = k - blk * (uint32_t)Q;
+  const uint32_t y = blk / W8;
+  const int x0 = (int)(blk - y * W8) * 8;
+  float4 v[8];
+#pragma unroll
+  for (int i = 0; i < 8; i++)
+    v[i] = x0 + i < W ? src[((int64_t)y * W + x0 + i) * Q + q] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  const int64_t run = 4 * ((int64_t)blk * Q + q);  // the thread's first run of 8 pixels
+  if constexpr (E == LV_FP8_E4M3) {
+    ChanScale cs[4];
+#pragma unroll
+    for (int c = 0; c < 4; c++) cs[c].set(__uint_as_float(amax[4 * q + c]));
+    const bool plain = cs[0].rc != 0.0f && cs[1].rc != 0.0f && cs[2].rc != 0.0f && cs[3].rc != 0.0f;
+    if (blk == 0)
+#pragma unroll
+      for (int c = 0; c < 4; c++) scales[4 * q + c] = cs[c].sc;
+    uint4 o[2];
+    uint32_t* const ow = reinterpret_cast<uint32_t*>(o);
+#pragma unroll
+    for (int c = 0; c < 4; c++) {
+      float x[8];
+#pragma unroll
+      for (int i = 0; i < 8; i++) {
+        const float u = c == 0 ? v[i].x : c == 1 ? v[i].y : c == 2 ? v[i].z : v[i].w;
+        x[i] = plain ? cs[c].div(u) : u / cs[c].sc;
+      }
+      ow[2 * c] = e4m3x2(x[0], x[1]) | (e4m3x2(x[2], x[3]) << 16);
+      ow[2 * c + 1] = e4m3x2(x[4], x[5]) | (e4m3x2(x[6], x[7]) << 16);
+    }
+    uint4* const d = reinterpret_cast<uint4*>(static_cast<uint2*>(dst) + run);
+    d[0] = o[0];
+    d[1] = o[1];
+  } else {
+#pragma unroll
+    for (int c = 0; c < 4; c++) {
+      float x[8];
+#pragma unroll
+      for (int i = 0; i < 8; i++) x[i] = c == 0 ? v[i].x : c == 1 ? v[i].y : c == 2 ? v[i].z : v[i].w;
+      if constexpr (E == LV_F32) {
+        float4* const d = static_cast<float4*>(dst) + 2 * (run + c);
+        d[0] = make_float4(x[0], x[1], x[2], x[3]);
+        d[1] = make_float4(x[4], x[5], x[6], x[7]);
+      } else {
+        uint4 o;
+        o.x = (uint32_t)to_bf16(x[0]) | ((uint32_t)to_bf16(x[1]) << 16);
+        o.y = (uint32_t)to_bf16(x[2]) | ((uint32_t)to_bf16(x[3]) << 16);
+        o.z = (uint32_t)to_bf16(x[4]) | ((uint32_t)to_bf16(x[5]) << 16);
+        o.w = (uint32_t)to_bf16(x[6]) | ((uint32_t)to_bf16(x[7]) << 16);
+        static_cast<uint4*>(dst)[run + c] = o;
+      }
+    }
   }
 }
 
@@ -173,31 +340,59 @@ __global__ __launch_bounds__(256) void encode_px8_kernel(const float* __restrict
 
 hipError_t launch_encode(const float* src, int64_t pixels, int D, lv_dtype dtype, void* dst,
                          float* scales, float* tmp_absmax, hipStream_t s, int W) {
-  int64_t total = pixels * (int64_t)D;
+  const int64_t total = pixels * (int64_t)D;
   if (total == 0) return hipSuccess;
-  if (map_px8(dtype)) {
-    const lv_dtype el = map_elem(dtype);
-    if (el == LV_FP8_E4M3) {
-      uint32_t* amax = reinterpret_cast<uint32_t*>(tmp_absmax);
-      hipLaunchKernelGGL(zero_kernel, dim3((D + 255) / 256), dim3(256), 0, s, amax, D);
-      int rows = 512;
-      hipLaunchKernelGGL(absmax_kernel, dim3((unsigned)((pixels + rows - 1) / rows), (D + 63) / 64),
-                         dim3(256), 0, s, src, pixels, D, rows, amax);
-      hipLaunchKernelGGL(scale_kernel, dim3((D + 255) / 256), dim3(256), 0, s, amax, D, scales);
-    }
-    const int64_t runs = pixels / W * ((W + 7) / 8) * (int64_t)D;
-    const unsigned nb = (unsigned)std::min<int64_t>((runs + 255) / 256, 65536);
-    if (el == LV_F32)
-      hipLaunchKernelGGL(encode_px8_kernel<LV_F32>, dim3(nb), dim3(256), 0, s, src, W, D, runs, scales, dst);
-    else if (el == LV_BF16)
-      hipLaunchKernelGGL(encode_px8_kernel<LV_BF16>, dim3(nb), dim3(256), 0, s, src, W, D, runs, scales, dst);
-    else
-      hipLaunchKernelGGL(encode_px8_kernel<LV_FP8_E4M3>, dim3(nb), dim3(256), 0, s, src, W, D, runs, scales,
-                         dst);
-    return hipGetLastError();
-  }
+  const lv_dtype el = map_elem(dtype);
+  const bool px8 = map_px8(dtype);
   if (dtype == LV_F32) {
     return hipMemcpyAsync(dst, src, (size_t)total * sizeof(float), hipMemcpyDeviceToDevice, s);
+  }
+  const int64_t runs = px8 ? pixels / W * ((W + 7) / 8) * (int64_t)D : 0;
+  // four channels per thread: D a multiple of 4, 16-byte loads (a pixel-block
+  // run of four channels is then 32 bytes or more in every element type), HWC
+  // codes in 4-byte stores, and thread indices that fit 32 bits
+  const bool quad = D % 4 == 0 && (uintptr_t)src % 16 == 0 &&
+                    (px8 ? (uintptr_t)dst % 16 == 0 && runs / 4 < 0xFFFFFF00ll : (uintptr_t)dst % 4 == 0);
+  const int Q = D / 4;
+  const float4* const src4 = reinterpret_cast<const float4*>(src);
+  uint32_t* const amax = reinterpret_cast<uint32_t*>(tmp_absmax);
+  if (el == LV_FP8_E4M3) {
+    // the per-channel absmax starts at zero (a kernel, not a memset: callers
+    // may capture the launches in a graph)
+    hipLaunchKernelGGL(zero_kernel, dim3((D + 255) / 256), dim3(256), 0, s, amax, D);
+    if (quad) {
+      // one block per CU at most: the channels' atomics of all blocks meet
+      const unsigned nb = (unsigned)std::max<int64_t>((Q + 1023) / 1024, std::min<int64_t>((total / 4 + 4095) / 4096, 256));
+      hipLaunchKernelGGL(absmax4_kernel, dim3(nb), dim3(1024), 4 * (size_t)D, s, src4, total / 4, Q, amax);
+    } else {
+      const int rows = 512;
+      hipLaunchKernelGGL(absmax_kernel, dim3((unsigned)((pixels + rows - 1) / rows), (D + 63) / 64), dim3(256), 0,
+                         s, src, pixels, D, rows, amax);
+      hipLaunchKernelGGL(scale_kernel, dim3((D + 255) / 256), dim3(256), 0, s, amax, D, scales);
+    }
+  }
+  if (px8 && quad) {
+    const unsigned nb = (unsigned)((runs / 4 + 255) / 256);
+    const auto kernel = el == LV_F32    ? encode_px8_quad_kernel<LV_F32>
+                        : el == LV_BF16 ? encode_px8_quad_kernel<LV_BF16>
+                                        : encode_px8_quad_kernel<LV_FP8_E4M3>;
+    hipLaunchKernelGGL(kernel, dim3(nb), dim3(256), 0, s, src4, W, Q, (uint32_t)(runs / 4), amax, scales, dst);
+    return hipGetLastError();
+  }
+  if (px8) {
+    const unsigned nb = (unsigned)std::min<int64_t>((runs + 255) / 256, 65536);
+    const auto kernel = el == LV_F32    ? encode_px8_kernel<LV_F32>
+                        : el == LV_BF16 ? encode_px8_kernel<LV_BF16>
+                                        : encode_px8_kernel<LV_FP8_E4M3>;
+    hipLaunchKernelGGL(kernel, dim3(nb), dim3(256), 0, s, src, W, D, runs, scales, dst);
+    return hipGetLastError();
+  }
+  if (el == LV_FP8_E4M3 && quad) {
+    const int64_t want = (total / 4 + 255) / 256;
+    const unsigned nb = (unsigned)std::max<int64_t>((Q + 255) / 256, std::min<int64_t>(want, 4096));
+    hipLaunchKernelGGL(encode_fp8_quad_kernel, dim3(nb), dim3(256), 0, s, src4, total / 4, Q, amax, scales,
+                       static_cast<uint32_t*>(dst));
+    return hipGetLastError();
   }
   // 8 elements per thread where source and destination allow 16-byte (BF16)
   // or 8-byte (FP8) accesses, the rest one per thread
@@ -209,24 +404,14 @@ hipError_t launch_encode(const float* src, int64_t pixels, int D, lv_dtype dtype
   const unsigned tb = (unsigned)((total - first + 255) / 256);
   if (dtype == LV_BF16) {
     if (groups)
-      hipLaunchKernelGGL(encode_bf16_vec_kernel, dim3(vb), dim3(256), 0, s,
-                         reinterpret_cast<const float4*>(src), groups, static_cast<uint4*>(dst));
+      hipLaunchKernelGGL(encode_bf16_vec_kernel, dim3(vb), dim3(256), 0, s, src4, groups, static_cast<uint4*>(dst));
     if (tb)
       hipLaunchKernelGGL(encode_bf16_kernel, dim3(tb), dim3(256), 0, s, src, first, total,
                          static_cast<uint16_t*>(dst));
     return hipGetLastError();
   }
-  // the per-channel absmax starts at zero (a kernel, not a memset: callers
-  // may capture the launches in a graph)
-  uint32_t* amax = reinterpret_cast<uint32_t*>(tmp_absmax);
-  hipLaunchKernelGGL(zero_kernel, dim3((D + 255) / 256), dim3(256), 0, s, amax, D);
-  int rows = 512;
-  hipLaunchKernelGGL(absmax_kernel, dim3((unsigned)((pixels + rows - 1) / rows), (D + 63) / 64),
-                     dim3(256), 0, s, src, pixels, D, rows, amax);
-  hipLaunchKernelGGL(scale_kernel, dim3((D + 255) / 256), dim3(256), 0, s, amax, D, scales);
   if (groups)
-    hipLaunchKernelGGL(encode_fp8_vec_kernel, dim3(vb), dim3(256), 0, s,
-                       reinterpret_cast<const float4*>(src), groups, D, scales,
+    hipLaunchKernelGGL(encode_fp8_vec_kernel, dim3(vb), dim3(256), 0, s, src4, groups, D, scales,
                        static_cast<uint2*>(dst));
   if (tb)
     hipLaunchKernelGGL(encode_fp8_kernel, dim3(tb), dim3(256), 0, s, src, first, total, D, scales,
