@@ -9,6 +9,7 @@
 // Within a block, each wave ranks its items in rounds of 64 in index order;
 // lanes holding the same digit are found with one wave ballot per digit bit,
 // so ranking needs no atomics and keeps input order among equal digits.
+#include <algorithm>
 #include <type_traits>
 
 #include "lv_internal.h"
@@ -34,26 +35,42 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, int bits, uint64_t a
 
 constexpr int kBins = 1 << kRadixBits;        // digit values per pass
 static_assert(kBins <= 2048, "the scan gives each of its 1024 threads at most two digits");
-constexpr int kWaveItems = kSortItems / 4;    // contiguous items per wave
-constexpr int kPerLane = kWaveItems / 64;     // items per lane, held in registers
-constexpr int kPerThread = kSortItems / kSortThreads;
-static_assert(kSortThreads == 256 && kWaveItems % 64 == 0, "four waves per block");
+static_assert(kSortThreads == 256, "four waves per block");
+
+// Items per block (kI below).  A block works through its items in rounds of 64
+// per wave, one after the other, so where there are too few blocks to fill the
+// chip smaller ones finish sooner: with 4 views of 10k items (12 blocks of 4096)
+// a scatter takes 6.9 us instead of 15.9, with 4 of 100k (100 blocks) 10.4
+// instead of 17.9.  From 128 blocks on the larger ones are as fast or faster:
+// they write longer runs per digit, in fewer histogram rows (1M items, 11-bit
+// digits, 245 blocks: anchors and 100 steps of diffusion 2.87 ms, 2.93 with
+// blocks of 1024).
+constexpr int kSmallSortItems = 1024;
+constexpr int kFewSortBlocks = 128;
+int sort_items(int nseg, int64_t max_len) {
+  return (int64_t)nseg * ((max_len + kSortItems - 1) / kSortItems) < kFewSortBlocks ? kSmallSortItems : kSortItems;
+}
+int sort_blocks(int nseg, int64_t max_len) {
+  const int items = sort_items(nseg, max_len);
+  return (int)((max_len + items - 1) / items);
+}
 
 // Digit counts of one block's items (LDS atomics: the order of counting does
 // not matter), written as the block's row hist[segment][block][digit].  All
 // of the block's keys are loaded before any is counted.
 // kB: digit values the LDS arrays hold (passes of at most 8 or 10 bits use
 // smaller arrays, so more blocks fit on a CU).
-template <int kB, typename K = uint32_t>
+template <int kB, int kI, typename K = uint32_t>
 __global__ __launch_bounds__(kSortThreads) void radix_hist_kernel(
     const K* __restrict__ keys, const uint32_t* __restrict__ seg_start,
     const uint32_t* __restrict__ seg_len, int shift, int bits, int nb, uint32_t* __restrict__ hist) {
+  constexpr int kPerThread = kI / kSortThreads;
   __shared__ uint32_t hs[kB];
   const int g = blockIdx.y, b = blockIdx.x, t = threadIdx.x;
   const int nbins = 1 << bits;
   const uint32_t mask = (uint32_t)nbins - 1u;
   const uint32_t len = seg_len[g];
-  const uint32_t base = (uint32_t)b * kSortItems;
+  const uint32_t base = (uint32_t)b * kI;
   const K* k = keys + seg_start[g];
   uint32_t d[kPerThread];
 #pragma unroll
@@ -73,37 +90,48 @@ __global__ __launch_bounds__(kSortThreads) void radix_hist_kernel(
 
 // Exclusive scan, per segment, over (digit, block) in digit-major order, of
 // counts stored block-major (hist[segment][block][digit]).  Thread t owns
-// digits [k t, k t + k): it sums its columns over the blocks, the digit totals
-// are scanned across the threads, and a second walk down the columns writes
-// each entry's start.  Rows are read whole by the block (coalesced).
+// digits [k t', k t' + k), t' = t mod (nbins / k), over the t / (nbins / k)-th
+// share of the rows (k = 2 for 2048 digits, else 1): it sums its columns over
+// its rows, the digit totals are scanned across the threads, and a second walk
+// down the columns writes each entry's start.  Rows are read whole by the
+// block (coalesced).
 __global__ __launch_bounds__(1024) void radix_scan_kernel(uint32_t* __restrict__ hist, int nb,
                                                           int bits) {
   __shared__ uint32_t part[1024 / 64];
+  __shared__ uint32_t sums[2][1024];  // column sums of each share
   const int g = blockIdx.x, t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int nbins = 1 << bits;
-  const int k = nbins > 1024 ? nbins / 1024 : 1;  // digits per thread (1 or 2)
-  const int d0 = k * t;
-  const bool own = d0 < nbins;
+  const int k = nbins > 1024 ? 2 : 1;          // digits per thread
+  const int cols = nbins / k, shares = 1024 / cols;
+  const int col = t & (cols - 1), share = t / cols, d0 = k * col;
+  const int r0 = (int)((int64_t)nb * share / shares), r1 = (int)((int64_t)nb * (share + 1) / shares);
   uint32_t* h = hist + (size_t)g * nb * nbins;
   uint32_t tot[2] = {0u, 0u};
-  if (own) {
-    int b = 0;
-    for (; b + 8 <= nb; b += 8) {
-      uint32_t x[8][2];
+  for (int b = r0; b < r1; b += 8) {
+    uint32_t x[8][2];
 #pragma unroll
-      for (int u = 0; u < 8; u++)
+    for (int u = 0; u < 8; u++)
 #pragma unroll
-        for (int j = 0; j < 2; j++) x[u][j] = j < k ? h[(size_t)(b + u) * nbins + d0 + j] : 0u;
+      for (int j = 0; j < 2; j++) x[u][j] = j < k && b + u < r1 ? h[(size_t)(b + u) * nbins + d0 + j] : 0u;
 #pragma unroll
-      for (int u = 0; u < 8; u++) {
-        tot[0] += x[u][0];
-        tot[1] += x[u][1];
-      }
+    for (int u = 0; u < 8; u++) {
+      tot[0] += x[u][0];
+      tot[1] += x[u][1];
     }
-    for (; b < nb; b++)
-      for (int j = 0; j < k; j++) tot[j] += h[(size_t)b * nbins + d0 + j];
   }
-  const uint32_t mine = tot[0] + tot[1];
+  sums[0][t] = tot[0];
+  sums[1][t] = tot[1];
+  __syncthreads();
+  // digit totals (threads of share 0) and this thread's rows' offset within its digits
+  uint32_t all[2] = {0u, 0u}, off[2] = {0u, 0u};
+  for (int q = 0; q < shares; q++)
+#pragma unroll
+    for (int j = 0; j < 2; j++) {
+      const uint32_t x = sums[j][q * cols + col];
+      all[j] += x;
+      off[j] += q < share ? x : 0u;
+    }
+  const uint32_t mine = share == 0 ? all[0] + all[1] : 0u;
   uint32_t incl = mine;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
@@ -111,33 +139,28 @@ __global__ __launch_bounds__(1024) void radix_scan_kernel(uint32_t* __restrict__
     if (lane >= o) incl += y;
   }
   if (lane == 63) part[w] = incl;
+  __syncthreads();  // also: the sums are read
+  uint32_t base = incl - mine;
+  for (int q = 0; q < w; q++) base += part[q];
+  if (share == 0) sums[0][col] = base;
   __syncthreads();
-  uint32_t run0 = incl - mine;
-  for (int q = 0; q < w; q++) run0 += part[q];
-  if (!own) return;
-  uint32_t run[2] = {run0, run0 + tot[0]};
-  int b = 0;
-  for (; b + 8 <= nb; b += 8) {
+  const uint32_t first = sums[0][col];
+  uint32_t run[2] = {first + off[0], first + all[0] + off[1]};
+  for (int b = r0; b < r1; b += 8) {
     uint32_t x[8][2];
 #pragma unroll
     for (int u = 0; u < 8; u++)
 #pragma unroll
-      for (int j = 0; j < 2; j++) x[u][j] = j < k ? h[(size_t)(b + u) * nbins + d0 + j] : 0u;
+      for (int j = 0; j < 2; j++) x[u][j] = j < k && b + u < r1 ? h[(size_t)(b + u) * nbins + d0 + j] : 0u;
 #pragma unroll
     for (int u = 0; u < 8; u++)
 #pragma unroll
       for (int j = 0; j < 2; j++)
-        if (j < k) {
+        if (j < k && b + u < r1) {
           h[(size_t)(b + u) * nbins + d0 + j] = run[j];
           run[j] += x[u][j];
         }
   }
-  for (; b < nb; b++)
-    for (int j = 0; j < k; j++) {
-      const uint32_t x = h[(size_t)b * nbins + d0 + j];
-      h[(size_t)b * nbins + d0 + j] = run[j];
-      run[j] += x;
-    }
 }
 
 // The same scan split over row chunks, for segments with many blocks (the scan
@@ -147,7 +170,8 @@ __global__ __launch_bounds__(1024) void radix_scan_kernel(uint32_t* __restrict__
 // part[segment][chunk][digit] holds first the chunk's column sums, then each
 // chunk's starting offset per digit.
 constexpr int kScanChunks = 16;
-constexpr int kChunkedRows = 64;  // rows per segment from which the split scan runs
+constexpr int kChunkedRows = 64;  // rows per share of a scan block from which the split scan runs
+bool split_scan(int nb, int bits) { return nb >= kChunkedRows * std::max(1, 1024 >> bits); }
 
 __global__ __launch_bounds__(1024) void radix_chunk_sum_kernel(const uint32_t* __restrict__ hist,
                                                                int nb, int bits,
@@ -244,27 +268,30 @@ __global__ __launch_bounds__(1024) void radix_chunk_write_kernel(uint32_t* __res
 // takes rect[s0 + val] (and its area, the count) to its output position.
 // kKeys false: the keys are not written (kout NULL), so LDS holds each
 // item's digit instead of its key (a smaller block footprint).
-template <int kB, bool kKeys = true, typename K = uint32_t>
+template <int kB, int kI, bool kKeys = true, typename K = uint32_t>
 __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
     const K* __restrict__ kin, const uint32_t* __restrict__ vin, K* __restrict__ kout,
     uint32_t* __restrict__ vout, const uint32_t* __restrict__ seg_start,
     const uint32_t* __restrict__ seg_len, int shift, int bits, int nb,
     const uint32_t* __restrict__ hist, SortPayload pl) {
   constexpr int kPer = kB / kSortThreads;          // digits per thread in the scan
+  constexpr int kWaveItems = kI / 4;               // contiguous items per wave
+  constexpr int kPerLane = kWaveItems / 64;        // items per lane, held in registers
+  constexpr int kPerThread = kI / kSortThreads;
   __shared__ uint16_t wc[4][kB];                    // per-wave counts, then local cursors
   __shared__ uint32_t gdelta[kB];                   // global minus local position, per digit
   // LDS keeps each item's key (16-bit keys, or 32-bit ones that are written
   // out) or only its digit
   typedef typename std::conditional<kKeys && sizeof(K) == 4, uint32_t, uint16_t>::type lk_t;
-  __shared__ lk_t lk[kSortItems];
-  __shared__ uint32_t lval[kSortItems];
+  __shared__ lk_t lk[kI];
+  __shared__ uint32_t lval[kI];
   __shared__ uint32_t wsum[kSortThreads / 64];
   const int g = blockIdx.y, b = blockIdx.x, t = threadIdx.x, w = t >> 6, lane = t & 63;
   const uint32_t s0 = seg_start[g];
   const uint32_t len = seg_len[g];
-  const uint32_t base = (uint32_t)b * kSortItems;
+  const uint32_t base = (uint32_t)b * kI;
   if (base >= len) return;  // whole block idle (uniform)
-  const uint32_t items = min(len - base, (uint32_t)kSortItems);
+  const uint32_t items = min(len - base, (uint32_t)kI);
   const uint32_t lo = base + w * kWaveItems;
   const uint32_t hi = min(len, lo + kWaveItems);  // lo >= hi: the wave has no items
   const uint32_t mask = (1u << bits) - 1u;
@@ -822,7 +849,7 @@ hipError_t launch_depth_ties(const uint32_t* key, uint32_t* val, uint2* rect, ui
 }
 
 size_t sort_hist_size(int nseg, int64_t max_len) {
-  int64_t nb = (max_len + kSortItems - 1) / kSortItems;
+  int64_t nb = sort_blocks(nseg, max_len);
   if (nb < 1) nb = 1;
   if (nb >= kChunkedRows) nb += kScanChunks;  // the split scan's chunk sums
   return (size_t)nseg * kBins * (size_t)nb;
@@ -836,7 +863,7 @@ hipError_t radix_sort_t(K* k0, uint32_t* v0, K* k1, uint32_t* v1, const uint32_t
                         bool iota_values) {
   *in_second = false;
   if (nseg == 0 || max_len == 0 || bits == 0) return hipSuccess;
-  int nb = (int)((max_len + kSortItems - 1) / kSortItems);
+  const int nb = sort_blocks(nseg, max_len);
   K *ki = k0, *ko = k1;
   uint32_t *vi = v0, *vo = v1;
   // fewest passes of at most kRadixBits bits, widths balanced
@@ -847,17 +874,12 @@ hipError_t radix_sort_t(K* k0, uint32_t* v0, K* k1, uint32_t* v1, const uint32_t
     K* const kout = (p + 1 < passes || keys_last) ? ko : nullptr;
     const uint32_t* const vin = p == 0 && iota_values ? nullptr : vi;
     const SortPayload pl = p + 1 < passes ? SortPayload{} : payload;
-    if (pb <= 8) {
-      hipLaunchKernelGGL((radix_hist_kernel<256, K>), dim3(nb, nseg), dim3(kSortThreads), 0, s, ki,
-                         seg_start, seg_len, shift, pb, nb, hist);
-    } else if (pb <= 10) {
-      hipLaunchKernelGGL((radix_hist_kernel<1024, K>), dim3(nb, nseg), dim3(kSortThreads), 0, s, ki,
-                         seg_start, seg_len, shift, pb, nb, hist);
-    } else {
-      hipLaunchKernelGGL((radix_hist_kernel<kBins, K>), dim3(nb, nseg), dim3(kSortThreads), 0, s, ki,
-                         seg_start, seg_len, shift, pb, nb, hist);
-    }
-    if (nb >= kChunkedRows) {
+    const bool small = sort_items(nseg, max_len) == kSmallSortItems;
+    const auto hk = pb <= 8    ? (small ? radix_hist_kernel<256, kSmallSortItems, K> : radix_hist_kernel<256, kSortItems, K>)
+                    : pb <= 10 ? (small ? radix_hist_kernel<1024, kSmallSortItems, K> : radix_hist_kernel<1024, kSortItems, K>)
+                               : (small ? radix_hist_kernel<kBins, kSmallSortItems, K> : radix_hist_kernel<kBins, kSortItems, K>);
+    hipLaunchKernelGGL(hk, dim3(nb, nseg), dim3(kSortThreads), 0, s, ki, seg_start, seg_len, shift, pb, nb, hist);
+    if (split_scan(nb, pb)) {
       uint32_t* part = hist + (size_t)nseg * nb * ((size_t)1 << pb);  // sort_hist_size has room for it
       hipLaunchKernelGGL(radix_chunk_sum_kernel, dim3(kScanChunks, nseg), dim3(1024), 0, s, hist, nb, pb,
                          part);
@@ -867,19 +889,13 @@ hipError_t radix_sort_t(K* k0, uint32_t* v0, K* k1, uint32_t* v1, const uint32_t
     } else {
       hipLaunchKernelGGL(radix_scan_kernel, dim3(nseg), dim3(1024), 0, s, hist, nb, pb);
     }
-    if (pb <= 8) {
-      hipLaunchKernelGGL((radix_scatter_kernel<256, true, K>), dim3(nb, nseg), dim3(kSortThreads), 0, s, ki,
-                         vin, kout, vo, seg_start, seg_len, shift, pb, nb, hist, pl);
-    } else if (pb <= 10 && !kout) {
-      hipLaunchKernelGGL((radix_scatter_kernel<1024, false, K>), dim3(nb, nseg), dim3(kSortThreads), 0,
-                         s, ki, vin, kout, vo, seg_start, seg_len, shift, pb, nb, hist, pl);
-    } else if (pb <= 10) {
-      hipLaunchKernelGGL((radix_scatter_kernel<1024, true, K>), dim3(nb, nseg), dim3(kSortThreads), 0, s, ki,
-                         vin, kout, vo, seg_start, seg_len, shift, pb, nb, hist, pl);
-    } else {
-      hipLaunchKernelGGL((radix_scatter_kernel<kBins, true, K>), dim3(nb, nseg), dim3(kSortThreads), 0, s, ki,
-                         vin, kout, vo, seg_start, seg_len, shift, pb, nb, hist, pl);
-    }
+    const bool digits = pb > 8 && pb <= 10 && !kout;  // only the digits go through LDS
+    const auto sk = pb <= 8    ? (small ? radix_scatter_kernel<256, kSmallSortItems, true, K> : radix_scatter_kernel<256, kSortItems, true, K>)
+                    : digits   ? (small ? radix_scatter_kernel<1024, kSmallSortItems, false, K> : radix_scatter_kernel<1024, kSortItems, false, K>)
+                    : pb <= 10 ? (small ? radix_scatter_kernel<1024, kSmallSortItems, true, K> : radix_scatter_kernel<1024, kSortItems, true, K>)
+                               : (small ? radix_scatter_kernel<kBins, kSmallSortItems, true, K> : radix_scatter_kernel<kBins, kSortItems, true, K>);
+    hipLaunchKernelGGL(sk, dim3(nb, nseg), dim3(kSortThreads), 0, s, ki, vin, kout, vo, seg_start, seg_len, shift, pb,
+                       nb, hist, pl);
     shift += pb;
     K* tk = ki;
     ki = ko;
@@ -913,7 +929,7 @@ hipError_t launch_hist_ranges(const uint32_t* hist, const uint32_t* seg_start,
                               const uint32_t* seg_len, int nseg, int64_t max_len, int bits,
                               int tiles_stride, uint2* ranges, hipStream_t s) {
   if (nseg == 0 || tiles_stride == 0) return hipSuccess;
-  const int nb = (int)((max_len + kSortItems - 1) / kSortItems);
+  const int nb = sort_blocks(nseg, max_len);
   hipLaunchKernelGGL(hist_ranges_kernel, dim3((unsigned)((tiles_stride + 255) / 256), nseg),
                      dim3(256), 0, s, hist, seg_start, seg_len, nb, bits, tiles_stride, ranges);
   return hipGetLastError();
