@@ -4,11 +4,11 @@
 // pixel (Eq. 1), and add w_i(p) F(p) and w_i(p) into the per-Gaussian
 // accumulators U_i and beta_i.  W is never materialised.
 //
-// One workgroup = one wave64 = one 8x8 quadrant of a 16x16 tile (one pixel
-// per lane) for one group of up to 64 channels; with several groups, one
-// wave per 16x8 half tile for all of them (blend_pair_kernel, two pixels per
-// lane).  Waves never wait for each other.  Per step of 64 Gaussians of the
-// tile's list:
+// One workgroup = one 8x8 quadrant of a 16x16 tile (one pixel per lane) for one
+// group of up to 64 channels, as one wave64 that walks and flushes in turn or
+// two that share the work; with several groups, one wave per 16x8 half tile for
+// all of them (blend_pair_kernel, two pixels per lane).  Workgroups never wait
+// for each other.  Per step of 64 Gaussians of the tile's list:
 //   0. lane j loads Gaussian j's record (vector loads, all in flight
 //      together), leaves it in LDS and tests whether its alpha >= 1/255
 //      region can touch the quadrant (exact minimum of the conic over the
@@ -16,8 +16,8 @@
 //   A. walk: a scalar loop over the hit Gaussians in order; each lane
 //      evaluates the Gaussian at its pixel (the record read from LDS at one
 //      address, a broadcast), every decision in the S32 sequence;
-//   B. a Gaussian with some w > 0 takes the next of 32 LDS rows (its weights
-//      at the 64 pixels).  A full set of rows (and the last, partial one) is
+//   B. the Gaussian takes the next of 32 LDS rows (its weights at the 64
+//      pixels; in the pair and render kernels only if some w > 0).  A full set of rows (and the last, partial one) is
 //      flushed: U_rows += W_rows F on the matrix cores, one global atomic per
 //      (Gaussian, channel); beta (the rows' sums, in exact fixed point, once
 //      for all feature sets that take the same views) and the tail channels
@@ -132,8 +132,7 @@ struct Walk {
   float pxo, pyo;  // this lane's pixel, relative to the tile
   float ocx, ocy;  // first pixel centre of the tile, ox + 0.5, oy + 0.5
   float qx0, qy0;  // the quadrant's first pixel, relative to the tile
-  float T;
-  bool alive;
+  float T;         // transmittance; 0 once the pixel is done, or outside the image
 };
 
 __device__ __forceinline__ void walk_init(const Quad& q, int lane, Walk& s) {
@@ -145,57 +144,124 @@ __device__ __forceinline__ void walk_init(const Quad& q, int lane, Walk& s) {
   s.ocy = (float)oy + 0.5f;
   s.qx0 = (float)(q.qx - ox);
   s.qy0 = (float)(q.qy - oy);
-  s.T = 1.0f;
-  s.alive = px < q.g.W && py < q.g.H;
+  s.T = px < q.g.W && py < q.g.H ? 1.0f : 0.0f;
 }
 
-// Step 0: records of Gaussians [base, base + cnt) one per lane, centres made
-// tile-relative and left in rs[lane] = {(cx, cy, L11, L12), (L22, opacity,
-// tau, -)} for the walk; the hit mask (the alpha >= 1/255 region can touch
-// the quadrant).
-// perm (nullable): storage -> caller order; my_id is then the caller's index
-// (loaded beside the records).
-__device__ __forceinline__ uint64_t step_records(const Rec* __restrict__ vrec,
-                                                 const uint32_t* __restrict__ ids, uint32_t base,
-                                                 int cnt, int lane, const Walk& s, uint32_t& my_id,
-                                                 float4 (*rs)[2],
-                                                 const uint32_t* __restrict__ perm = nullptr) {
-  float4 q0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  float4 q1 = make_float4(0.0f, 0.0f, -1.0f, 0.0f);
-  my_id = 0;
-  if (lane < cnt) {
-    const uint32_t id = ids[base + lane];
-    my_id = perm ? perm[id] : id;
-    q0 = vrec[id].r0;
-    q1 = vrec[id].r1;
-    // centre relative to the tile (see Rec)
-    const uint32_t lo = __float_as_uint(q1.w);
-    q0.x = (q0.x - s.ocx) + __uint_as_float(lo << 16);
-    q0.y = (q0.y - s.ocy) + __uint_as_float(lo & 0xFFFF0000u);
+// The records of a tile's list, one step of 64 entries after the other.
+// kAhead, for a wave that issues no atomics of its own: a step's ids are loaded
+// two steps ahead and its records one step ahead (past the list's end: its last
+// entry again, never used).  A wave that does issue atomics gains nothing from
+// it: the vector memory counter is in order, so the loads' data would be waited
+// for together with the atomics.
+template <bool kAhead>
+struct Steps {
+  const Rec* vrec;
+  const uint32_t* ids;
+  const uint32_t* perm;  // nullable: storage -> caller order, for the ids handed out
+  uint32_t end;          // the list's end
+  uint32_t id1, id2;     // this lane's entries of the next step and the one after
+  uint32_t out1;         // the next step's id as handed out
+  float4 n0, n1;         // the next step's record
+  __device__ __forceinline__ uint32_t id_at(uint32_t e) const { return ids[e < end ? e : end - 1]; }
+  __device__ __forceinline__ void load(uint32_t id) {
+    out1 = perm ? perm[id] : id;
+    n0 = vrec[id].r0;
+    n1 = vrec[id].r1;
   }
+  __device__ __forceinline__ void start(const Rec* r, const uint32_t* i, uint2 rg, int lane,
+                                        const uint32_t* p = nullptr) {
+    vrec = r;
+    ids = i;
+    perm = p;
+    end = rg.y;
+    if constexpr (kAhead) {
+      id1 = id_at(rg.x + lane);
+      id2 = id_at(rg.x + kChunk + lane);
+      load(id1);
+    }
+  }
+  // the step from entry `base`: this lane's id and record
+  __device__ __forceinline__ void next(uint32_t base, int lane, uint32_t& id, float4& q0, float4& q1) {
+    if constexpr (!kAhead) load(id_at(base + lane));
+    id = out1;
+    q0 = n0;
+    q1 = n1;
+    if constexpr (kAhead) {
+      id1 = id2;
+      id2 = id_at(base + 2 * kChunk + lane);
+      load(id1);
+    }
+  }
+};
+
+// The step from entry `base`: this lane's record, its centre made tile-relative,
+// left in rs[lane] = {(cx, cy, L11, L12), (L22, opacity, tau, -)} for the walk;
+// the hit mask (the alpha >= 1/255 region can touch the quadrant).
+template <bool kAhead>
+__device__ __forceinline__ uint64_t step_records(Steps<kAhead>& st, uint32_t base, int lane, const Walk& s,
+                                                 uint32_t& my_id, float4 (*rs)[2]) {
+  float4 q0, q1;
+  st.next(base, lane, my_id, q0, q1);
+  const uint32_t lo = __float_as_uint(q1.w);  // centre relative to the tile (see Rec)
+  q0.x = (q0.x - s.ocx) + __uint_as_float(lo << 16);
+  q0.y = (q0.y - s.ocy) + __uint_as_float(lo & 0xFFFF0000u);
   rs[lane][0] = q0;
   rs[lane][1] = q1;
   const float X0 = s.qx0 - q0.x, Y0 = s.qy0 - q0.y;
-  const bool hit = lane < cnt && region_hits(q0, q1, X0, X0 + 7.0f, Y0, Y0 + 7.0f);
+  const bool hit = base + lane < st.end && region_hits(q0, q1, X0, X0 + 7.0f, Y0, Y0 + 7.0f);
   return __ballot(hit);
 }
 
-// One step of the walk: the Gaussian of record (a, b) = ((cx, cy, L11, L12),
-// (L22, opacity, -, -)) at this lane's pixel.  take: it contributes here
-// (then w = alpha T > 0).
-__device__ __forceinline__ float walk_rec(const float4& a, const float4& b, Walk& s, bool& take) {
-  const float dx = s.pxo - a.x, dy = s.pyo - a.y;
+// Barrier of a workgroup's waves that orders their LDS accesses only: loads and
+// atomics stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Up to this many quadrants, a quadrant gets two waves, one that walks and one
+// that flushes, rather than one that does both in turn: four quadrants per SIMD
+// leave room for the second wave, and the launch lasts as long as its longest
+// quadrant.  Past it the chip is full either way and the second wave and queue
+// only take the first ones' room.  Launch of 512x384 views (3072 quadrants
+// each), one wave / two: 1 mask channel, 200k Gaussians, 1 view 113 / 86 us, 2
+// views 115 / 121, 8 views 260 / 343; render, D = 16, 50k Gaussians, 1 view 67 /
+// 60, 2 views 81 / 90.
+constexpr int64_t kFewQuadrants = 4096;
+
+// Orders one wave's LDS accesses.
+__device__ __forceinline__ void lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// One step of the walk: the weight w = alpha T of the Gaussian of record
+// (a, b) = ((cx, cy, L11, L12), (L22, opacity, -, -)) at the pixel (pxo, pyo),
+// 0 where it takes no part.  A pixel that is done (the Gaussian that would take
+// its transmittance below 1e-4, which is not counted, has been met) or outside
+// the image has T = 0; otherwise T >= 1e-4, so a counted weight is at least
+// 1e-4 / 255 and w != 0 says that the Gaussian is counted.  No masks besides T:
+// a wave's hits are a serial chain, and a wave issues an instruction every four
+// cycles at most, so the chain costs what its instructions do: with the state in
+// lane masks, a branch around the row and its id stored by the lane that holds
+// it, an uplift of 10k Gaussians into 4 views of 128x128, D = 8, took 165 us for
+// the launch instead of 133, and one of a mask (200k Gaussians, 50 views of
+// 512x384) 1.84 ms instead of 1.45.
+__device__ __forceinline__ float blend_step(const float4& a, const float2& b, float pxo, float pyo, float& T) {
+  const float dx = pxo - a.x, dy = pyo - a.y;
   const float u = __builtin_fmaf(a.w, dy, a.z * dx), w = b.x * dy;
   const float al = fminf(kAlphaMax, b.y * exp_neg(-__builtin_fmaf(u, u, w * w)));
-  const bool ok = s.alive && al >= kAlphaMin;
-  const float Tn = s.T * (1.0f - al);
-  const bool stop = ok && Tn < kTEps;
-  take = ok && !stop;
-  const float wj = take ? al * s.T : 0.0f;
-  s.T = take ? Tn : s.T;
-  s.alive = s.alive && !stop;
+  const float ac = al >= kAlphaMin ? al : 0.0f;
+  const float Tn = T * (1.0f - ac);  // T where the Gaussian is skipped
+  const bool on = Tn >= kTEps;
+  const float wj = on ? ac * T : 0.0f;
+  T = on ? Tn : 0.0f;
   return wj;
 }
+
+// Lanes with x != 0.
+__device__ __forceinline__ uint64_t nonzero(float x) { return __builtin_amdgcn_ballot_w64(x != 0.0f); }
 
 // ---------------------------------------------------------------- wide kernel
 // Any number of feature sets; the workgroup's channel group has up to 64
@@ -493,28 +559,49 @@ __device__ __forceinline__ void batch_scatter(const GroupLanes& L, bool two, int
     batch_scatter_t<DT, false>(L, two, count, ring_gid, lane, acc0, acc1);
 }
 
-// One channel group (at most 64 + 4 channels): one wave per (view,
+// One channel group (at most 64 + 4 channels), one workgroup per (view,
 // quadrant); the group's F fragments are staged once in registers.  Several
-// groups run on blend_pair_kernel below.  Occupancy: waves per SIMD the
-// register allocation must allow (the walk is latency-bound; more resident
-// waves hide it).  BF16 maps need no low operand halves, so they fit four.
+// groups run on blend_pair_kernel below.  The walk is a serial chain of
+// instructions, the flush waits for the atomics' queue.  kTwo: the first wave
+// walks and fills two queues of 32 rows in turn, the second flushes the one just
+// filled, and they meet at one barrier per queue, which neither loads nor atomics
+// in flight hold up; else one wave does both with one queue.  Two waves where
+// the launch has few quadrants (kFewQuadrants) or the group has a matrix block,
+// whose flush is long.  Launch, the walk before blend_step / one wave / two: 200k
+// Gaussians, 50 views of 512x384, D = 64 in BF16 3.57 / 3.52 / 3.42 ms (the
+// atomics' rate bounds it), D = 1 1.84 / 1.45 / 1.94; 10k Gaussians, 4 views of
+// 128x128, D = 8 165 / 133 / 82 us; 50k Gaussians, nine launches of a 333x251
+// view, D = 37 455 / 445 / 390 us.  Occupancy: waves per SIMD the register
+// allocation must allow.  BF16 maps need no low operand halves, so they fit four.
 template <lv_dtype DT>
 constexpr int wide_waves() {
   return DT == LV_BF16 ? 4 : 3;
 }
 
-template <lv_dtype DT, bool PX>
-__global__ __launch_bounds__(64, (wide_waves<DT>())) void blend_wide_kernel(
+template <lv_dtype DT, bool PX, bool kTwo>
+__global__ __launch_bounds__(kTwo ? 128 : 64, (wide_waves<DT>())) void blend_wide_kernel(
     const Rec* __restrict__ rec, const uint32_t* __restrict__ ids, const uint2* __restrict__ ranges,
     const ViewGeom* __restrict__ geom, int64_t n, int tiles_stride, int nviews,
     const SetDesc* __restrict__ sets, const ChanGroup* __restrict__ groups, int ngroups) {
-  constexpr int G = kChunk;
   constexpr bool kSplitF = DT == LV_F32;  // BF16 maps and FP8 codes are exact in one BF16 operand
-  __shared__ __align__(16) float Wt[32 * kWtPitch];  // queued Gaussians: [row][pixel]
+  constexpr int kQueues = kTwo ? 2 : 1;
+  __shared__ __align__(16) float Wts[kQueues][32 * kWtPitch];  // queued Gaussians: [row][pixel]
+  __shared__ uint64_t Pix[kQueues];                            // pixels used by the rows
+  __shared__ int Count[kQueues];                               // rows, + 64 with the last ones
+  // ids of the hits in order, hit k at k mod kIds: a queue's rows are
+  // consecutive hits, and a step's ids are written all at once, at most 64 past
+  // the queues
+  constexpr int kIds = kTwo ? 256 : 128;
+  __shared__ uint32_t Ids[kIds];
   __shared__ float4 Rs[kChunk][2];                   // the step's records
+  // tail channels: their features per pixel, summed against the queued rows at
+  // each flush
+  __shared__ __align__(16) float Ft[kMaxTail * 64];
   Quad q;
   if (!decode_quad(ranges, geom, tiles_stride, nviews, ngroups, q)) return;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  // two waves: the first walks, the second flushes
+  const bool flushes = !kTwo || __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) != 0;
   const bool fixedU = sets[0].fixed != 0;  // one accumulation mode per launch (wave-uniform)
   const int px = q.qx + (lane & 7), py = q.qy + (lane >> 3);
   const bool inside = px < q.g.W && py < q.g.H;
@@ -533,69 +620,60 @@ __global__ __launch_bounds__(64, (wide_waves<DT>())) void blend_wide_kernel(
   }
   const ChanGroup& last = groups[q.cg];
   const int ntail = last.ntail;
-  // tail channels: their features per pixel in LDS (Ft[t][pixel]), summed
-  // against the ring rows at each flush
-  __shared__ __align__(16) float Ft[kMaxTail * 64];
-  float* tout[kMaxTail];
-  int tD[kMaxTail];
   bool any_tail = false;
-#pragma unroll
-  for (int t = 0; t < kMaxTail; t++) {
-    float ft = 0.0f;
-    tout[t] = nullptr;
-    tD[t] = 0;
-    if (t < ntail && map_of(sets[last.tset[t]], q.v)) {
-      const SetDesc& sd = sets[last.tset[t]];
-      const int c = last.tc[t];
-      float sc = 1.0f;
-      if constexpr (DT == LV_FP8_E4M3) sc = gptr(sd.scales)[(int64_t)(sd.view_base + q.v) * sd.D + c];
-      const int64_t idx = inside ? map_index<PX>(py, px, q.g.W, sd.stride, c) : 0;
-      const float x = load_feature<DT>(map_of(sd, q.v), idx, sc);  // no branch around the load
-      ft = inside ? x : 0.0f;
-      tout[t] = u_elem(sd.U, c, fixedU);
-      tD[t] = sd.D;
-      any_tail = true;
-    }
-    Ft[t * 64 + lane] = ft;
-  }
+  for (int t = 0; t < ntail; t++) any_tail = any_tail || map_of(sets[last.tset[t]], q.v) != nullptr;
   if (!has_main && !any_tail && !bsets && !ssets) return;  // wave-uniform: nothing here takes the view
 
-  // the group's lanes and fragments once, in registers
+  float* tout[kMaxTail];
+  int tD[kMaxTail];
   GroupLanes L1;
   bf16x8 fh[2][4], fl[2][4];
   bool two1 = false;
-  {
-    const ChanGroup& grp = groups[q.cg];
-    const bool takes = group_lanes<DT>(grp, sets, q, lane, L1);
-    two1 = grp.width > 32;
-    if (takes) {
+  if (flushes) {
 #pragma unroll
-      for (int b = 0; b < 2; b++)
-#pragma unroll
-        for (int t = 0; t < 4; t++)
-          load_row8<DT, PX>(L1, b, q.qy + 2 * t + (lane >> 5), q.qx, q.g, fh[b][t], fl[b][t]);
+    for (int t = 0; t < kMaxTail; t++) {
+      float ft = 0.0f;
+      tout[t] = nullptr;
+      tD[t] = 0;
+      if (t < ntail && map_of(sets[last.tset[t]], q.v)) {
+        const SetDesc& sd = sets[last.tset[t]];
+        const int c = last.tc[t];
+        float sc = 1.0f;
+        if constexpr (DT == LV_FP8_E4M3) sc = gptr(sd.scales)[(int64_t)(sd.view_base + q.v) * sd.D + c];
+        const int64_t idx = inside ? map_index<PX>(py, px, q.g.W, sd.stride, c) : 0;
+        const float x = load_feature<DT>(map_of(sd, q.v), idx, sc);  // no branch around the load
+        ft = inside ? x : 0.0f;
+        tout[t] = u_elem(sd.U, c, fixedU);
+        tD[t] = sd.D;
+      }
+      Ft[t * 64 + lane] = ft;
     }
-    has_main = has_main && takes && __ballot(L1.outp[0] != nullptr || L1.outp[1] != nullptr) != 0ull;
+    lds_order();  // Ft is written and read by this wave only
+
+    // the group's lanes and fragments once, in registers
+    {
+      const ChanGroup& grp = groups[q.cg];
+      const bool takes = group_lanes<DT>(grp, sets, q, lane, L1);
+      two1 = grp.width > 32;
+      if (takes) {
+#pragma unroll
+        for (int b = 0; b < 2; b++)
+  #pragma unroll
+          for (int t = 0; t < 4; t++)
+            load_row8<DT, PX>(L1, b, q.qy + 2 * t + (lane >> 5), q.qx, q.g, fh[b][t], fl[b][t]);
+      }
+      has_main = has_main && takes && __ballot(L1.outp[0] != nullptr || L1.outp[1] != nullptr) != 0ull;
+    }
   }
+  // contributing pixels per row, where a set counts them
+  bool counting = ssets != 0;
+  for (int t = bsets; t; t &= t - 1) counting = counting || sets[__builtin_ctz(t)].counts != nullptr;
+  uint32_t ncontrib = 0u, nrows = 0u;  // this lane's rows (statistics)
 
-  // Gaussians with a contribution queue up in 32 LDS rows (row r: the
-  // Gaussian's weights at the 64 pixels in Wt, its id and its number of
-  // contributing pixels in Rg[r] / Rc[r], read into lane r's ring_gid /
-  // ring_cnt when the rows are flushed).  When the rows are
-  // full, and at the end, one flush: a batch of MFMAs (M = 32 rows) and one
-  // round of atomics per group, so the matrix products run on full rows
-  // whatever the number of contributing Gaussians per step of the walk; and
-  // the rows' sums (beta) and dot products with the tail channels, one row
-  // per lane pair, each lane summing half of the row in a fixed order.
-  int queued = 0;        // rows [0, queued) hold Gaussians
-  uint64_t pix = 0ull;   // pixels used by the queued rows
-  __shared__ uint32_t Rg[32], Rc[32];
-  uint32_t ring_gid = 0u, ring_cnt = 0u;
-
-  auto flush = [&](int count) {
-    __syncthreads();  // ring rows written (one wave per workgroup: orders LDS)
-    ring_gid = Rg[lane & 31];
-    ring_cnt = Rc[lane & 31];
+  // the rows of a queue, its first hit hit0, into the accumulators
+  auto flush = [&](const float* Wt, int count, uint64_t pix, uint32_t hit0) {
+    const uint32_t ring_gid = Ids[(hit0 + (uint32_t)(lane & 31)) % kIds];
+    uint32_t ring_cnt = 0u;
     const uint32_t rows = row_bits(pix);
     const float* wrow = Wt + (lane & 31) * kWtPitch + 8 * (lane >> 5);
     if (has_main) {
@@ -603,7 +681,7 @@ __global__ __launch_bounds__(64, (wide_waves<DT>())) void blend_wide_kernel(
       batch_mfma<kSplitF>(two1, rows, wrow, fh, fl, acc0, acc1);
       batch_scatter<DT>(L1, two1, count, ring_gid, lane, acc0, acc1, fixedU);
     }
-    if (bsets || any_tail) {
+    if (bsets || any_tail || counting) {
       // lane l: row l % 32, pixels [32 (l / 32), 32 (l / 32) + 32)
       const float* rp = Wt + (lane & 31) * kWtPitch + 32 * (lane >> 5);
       const float* fp = Ft + 32 * (lane >> 5);
@@ -627,9 +705,22 @@ __global__ __launch_bounds__(64, (wide_waves<DT>())) void blend_wide_kernel(
         }
       }
       bs += __shfl_xor(bs, 32, 64);
+      if (counting) {
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+          const float4 a = *reinterpret_cast<const float4*>(rp + 4 * k);
+          ring_cnt += (a.x != 0.0f ? 1u : 0u) + (a.y != 0.0f ? 1u : 0u) + (a.z != 0.0f ? 1u : 0u) +
+                      (a.w != 0.0f ? 1u : 0u);
+        }
+        ring_cnt += (uint32_t)__shfl_xor((int)ring_cnt, 32, 64);
+        if (lane < count) {
+          ncontrib += ring_cnt;
+          nrows += ring_cnt ? 1u : 0u;
+        }
+      }
 #pragma unroll
       for (int t = 0; t < kMaxTail; t++) ts[t] += __shfl_xor(ts[t], 32, 64);
-      if (lane < count) {  // lane r < 32: row r, whose id and count it holds
+      if (lane < count && bs != 0.0f) {  // lane r < 32: row r, whose id and count it holds
         for (int b = bsets; b; b &= b - 1) {
           const SetDesc& sd = sets[__builtin_ctz(b)];
           beta_atomic_add(sd.beta + ring_gid, bs);
@@ -640,72 +731,95 @@ __global__ __launch_bounds__(64, (wide_waves<DT>())) void blend_wide_kernel(
           if (tout[t] && ts[t] != 0.0f) u_atomic_add(tout[t], (int64_t)ring_gid * tD[t], ts[t], fixedU);
       }
     }
-    __syncthreads();  // rows read before they are written again
   };
+  // statistics go to every set whose statistics this work item takes
+  auto write_stats = [&](uint32_t covered) {
+    for (int o = 32; o > 0; o >>= 1) {
+      ncontrib += (uint32_t)__shfl_xor((int)ncontrib, o, 64);
+      nrows += (uint32_t)__shfl_xor((int)nrows, o, 64);
+    }
+    for (int t = ssets; t; t &= t - 1) add_stats(sets[__builtin_ctz(t)], lane, covered, ncontrib, nrows);
+  };
+
+  if (kTwo && flushes) {
+    uint32_t hit0 = 0u;  // the queue's first hit
+    for (int b = 0;; b ^= 1) {
+      lds_barrier();
+      const int handed = __builtin_amdgcn_readfirstlane(Count[b]), count = handed & 63;
+      if (count > 0) flush(Wts[b], count, Pix[b], hit0);
+      hit0 += 32u;
+      if (handed & 64) break;
+    }
+    write_stats(0u);
+    return;
+  }
 
   Walk s;
   walk_init(q, lane, s);
   uint64_t covered = 0ull;  // pixels with a contribution (statistics)
-  uint32_t ncontrib = 0u;   // contributions of the quadrant (statistics)
-  uint32_t nrows = 0u;      // Gaussians queued (statistics)
-  const Rec* vrec = rec + (int64_t)q.v * n;
-  for (uint32_t base = q.rg.x; base < q.rg.y; base += G) {
-    if (__ballot(s.alive) == 0ull) break;
-    const int cnt = (int)(q.rg.y - base < (uint32_t)G ? q.rg.y - base : (uint32_t)G);
-    uint32_t my_id;
-    const uint64_t hits = step_records(vrec, ids, base, cnt, lane, s, my_id, Rs);
-    if (!hits) continue;
-    __syncthreads();  // records in LDS (one wave per workgroup: orders LDS)
-
-    // the hit Gaussians in order (a scalar loop over the set bits; each
-    // record read from LDS, a broadcast, one hit ahead); each with a
-    // contribution takes the next ring row, a full ring is flushed
-    uint64_t h = hits;
-    int j = h ? (int)__builtin_ctzll(h) : 0;
-    float4 ra = Rs[j][0], rb = Rs[j][1];
-    while (h) {
-      h &= h - 1;
-      const int jn = h ? (int)__builtin_ctzll(h) : j;
-      // wj: this lane's weight (0 where it takes no part), msk: the lanes
-      // with a contribution
-      const float dx = s.pxo - ra.x, dy = s.pyo - ra.y;
-      const float u = __builtin_fmaf(ra.w, dy, ra.z * dx), w = rb.x * dy;
-      const float al = fminf(kAlphaMax, rb.y * exp_neg(-__builtin_fmaf(u, u, w * w)));
-      // the next record into the same registers (no copies between hits)
-      ra = Rs[jn][0];
-      rb = Rs[jn][1];
-      const float Tn = s.T * (1.0f - al);
-      const bool ok = s.alive && al >= kAlphaMin;
-      const bool stop = ok && Tn < kTEps;
-      const bool take = ok && !stop;
-      const uint64_t msk = __builtin_amdgcn_ballot_w64(take);
-      const float wj = take ? al * s.T : 0.0f;
-      s.T = take ? Tn : s.T;
-      s.alive = s.alive && !stop;
-      if (msk) {
-        covered |= msk;
-        ncontrib += (uint32_t)__popcll(msk);
-        nrows++;
-        Wt[queued * kWtPitch + lane] = wj;
-        if (lane == j) {  // lane j holds the Gaussian's id
-          Rg[queued] = my_id;
-          Rc[queued] = (uint32_t)__popcll(msk);
-        }
-        pix |= msk;
-        if (++queued == 32) {
-          flush(32);
-          queued = 0;
-          pix = 0ull;
-        }
+  Steps<kTwo> st;
+  st.start(rec + (int64_t)q.v * n, ids, q.rg, lane);
+  int b = 0, queued = 0;    // rows [0, queued) of queue b hold hits
+  uint32_t hits_done = 0u;  // hits before the step
+  uint32_t hit0 = 0u;       // the queue's first hit
+  float used = 0.0f;        // not 0 where the pixel has a weight in the queue
+  float* wrow = Wts[0] + lane;
+  // a full or last queue: flushed, or handed to the other wave, which has
+  // emptied the other queue when it arrives
+  auto hand_over = [&](int count) {
+    const uint64_t pix = nonzero(used);
+    covered |= pix;
+    if constexpr (kTwo) {
+      if (lane == 0) {
+        Pix[b] = pix;
+        Count[b] = count;
       }
-      j = jn;
+      lds_barrier();
+      b ^= 1;
+    } else {
+      lds_order();
+      if (count & 63) flush(Wts[0], count & 63, pix, hit0);
+      lds_order();
+      hit0 += 32u;
     }
+    queued = 0;
+    used = 0.0f;
+    wrow = Wts[b] + lane;
+  };
+  for (uint32_t base = q.rg.x; base < q.rg.y; base += kChunk) {
+    if (nonzero(s.T) == 0ull) break;
+    uint32_t my_id;
+    uint64_t h = step_records(st, base, lane, s, my_id, Rs);
+    if (!h) continue;
+    if ((h >> lane) & 1ull)
+      Ids[(hits_done + (uint32_t)__popcll(h & ((1ull << lane) - 1ull))) % kIds] = my_id;
+    hits_done += (uint32_t)__popcll(h);
+    lds_order();  // records in LDS
+    // the hit Gaussians in order (a scalar loop over the set bits; each
+    // record read from LDS, a broadcast, one hit ahead): each takes the next
+    // row, also where it has no contribution (its row is then zeros, which
+    // add nothing: nearly every hit has one, and a test would cost each hit
+    // more than the few rows); a full queue is handed over
+    int j = (int)__builtin_ctzll(h);
+    float4 ra = Rs[j][0];
+    float2 rb = *reinterpret_cast<const float2*>(&Rs[j][1]);
+    do {
+      h &= ~(1ull << j);
+      j = (int)__builtin_ctzll(h | (1ull << 63));  // 63 after the last: a readable record
+      const float4 ca = ra;
+      const float2 cb = rb;
+      ra = Rs[j][0];
+      rb = *reinterpret_cast<const float2*>(&Rs[j][1]);
+      const float wj = blend_step(ca, cb, s.pxo, s.pyo, s.T);
+      *wrow = wj;
+      wrow += kWtPitch;
+      used = fmaxf(used, wj);
+      if (++queued == 32) hand_over(32);
+    } while (h);
+    lds_order();  // the records are read before the next step's
   }
-  if (queued > 0) flush(queued);
-  // statistics go to every set whose statistics this work item takes
-  for (int b = ssets; b; b &= b - 1) {
-    add_stats(sets[__builtin_ctz(b)], lane, (uint32_t)__popcll(covered), ncontrib, nrows);
-  }
+  hand_over(queued + 64);
+  write_stats((uint32_t)__popcll(covered));
 }
 
 // ------------------------------------------------------------- pair kernel
@@ -747,23 +861,6 @@ __device__ __forceinline__ bool decode_pair(const uint2* __restrict__ ranges,
   q.qx = tx * kTile;
   q.qy = ty * kTile + half * 8;
   return q.qx < q.g.W && q.qy < q.g.H;
-}
-
-// Alpha-blending step at one pixel (offsets relative to the tile), as
-// walk_rec: take = the Gaussian contributes here, w = alpha T.
-__device__ __forceinline__ float blend_at(const float4& a, const float4& b, float pxo, float pyo,
-                                          float& T, bool& alive, bool& take) {
-  const float dx = pxo - a.x, dy = pyo - a.y;
-  const float u = __builtin_fmaf(a.w, dy, a.z * dx), w = b.x * dy;
-  const float al = fminf(kAlphaMax, b.y * exp_neg(-__builtin_fmaf(u, u, w * w)));
-  const bool ok = alive && al >= kAlphaMin;
-  const float Tn = T * (1.0f - al);
-  const bool stop = ok && Tn < kTEps;
-  take = ok && !stop;
-  const float wj = take ? al * T : 0.0f;
-  T = take ? Tn : T;
-  alive = alive && !stop;
-  return wj;
 }
 
 // group_lanes for a half tile (only the view matters)
@@ -850,14 +947,17 @@ __global__ __launch_bounds__(64, 2) void blend_pair_kernel(
   }
   if (!has_main && !any_tail && !bsets && !ssets) return;  // wave-uniform
 
+  float T0 = in0 ? 1.0f : 0.0f, T1 = in1 ? 1.0f : 0.0f;  // see Walk
+  uint64_t cov0 = 0ull, cov1 = 0ull;
+  uint32_t ncontrib = 0u, nrows = 0u;
   int queued = 0;
   uint64_t pix0 = 0ull, pix1 = 0ull;  // pixels of each quadrant used by the queued rows
-  uint32_t ring_gid = 0u, ring_cnt = 0u;
-
   auto flush = [&](int count) {
-    __syncthreads();  // ring rows written (one wave per workgroup: orders LDS)
-    ring_gid = Rg[lane & 31];
-    ring_cnt = Rc[lane & 31];
+    __syncthreads();  // queued rows written (one wave per workgroup: orders LDS)
+    const uint32_t ring_gid = Rg[lane & 31], ring_cnt = Rc[lane & 31];
+    cov0 |= pix0;
+    cov1 |= pix1;
+    nrows += (uint32_t)count;
     // bit r: pixel row r % 8 of quadrant r / 8; K-step t covers bits 2t, 2t + 1
     const uint32_t rows = row_bits(pix0) | (row_bits(pix1) << 8);
     const float* wrow = Wt + (lane & 31) * kPairPitch + 8 * (lane >> 5);
@@ -1011,13 +1111,9 @@ __global__ __launch_bounds__(64, 2) void blend_pair_kernel(
     __syncthreads();  // rows read before they are written again
   };
 
-  float T0 = 1.0f, T1 = 1.0f;
-  bool alive0 = in0, alive1 = in1;
-  uint64_t cov0 = 0ull, cov1 = 0ull;
-  uint32_t ncontrib = 0u, nrows = 0u;
   const Rec* vrec = rec + (int64_t)q.v * n;
   for (uint32_t base = q.rg.x; base < q.rg.y; base += G) {
-    if (__ballot(alive0 || alive1) == 0ull) break;
+    if ((nonzero(T0) | nonzero(T1)) == 0ull) break;
     const int cnt = (int)(q.rg.y - base < (uint32_t)G ? q.rg.y - base : (uint32_t)G);
     // lane j: record j, centre made tile-relative, left in LDS; hit masks of
     // the two quadrants
@@ -1044,31 +1140,25 @@ __global__ __launch_bounds__(64, 2) void blend_pair_kernel(
     while (h) {
       const int j = (int)__builtin_ctzll(h);
       h &= h - 1;
-      const float4 a = Rs[j][0], b = Rs[j][1];
-      bool t0 = false, t1 = false;
+      const float4 a = Rs[j][0];
+      const float2 b = *reinterpret_cast<const float2*>(&Rs[j][1]);
       float w0 = 0.0f, w1 = 0.0f;
-      if ((hits0 >> j) & 1ull) w0 = blend_at(a, b, pxo0, pyo, T0, alive0, t0);
-      if ((hits1 >> j) & 1ull) w1 = blend_at(a, b, pxo1, pyo, T1, alive1, t1);
-      const uint64_t m0 = __builtin_amdgcn_ballot_w64(t0), m1 = __builtin_amdgcn_ballot_w64(t1);
-      if (m0 | m1) {
-        cov0 |= m0;
-        cov1 |= m1;
-        const uint32_t c = (uint32_t)(__popcll(m0) + __popcll(m1));
-        ncontrib += c;
-        nrows++;
-        Wt[queued * kPairPitch + lane] = w0;
-        Wt[queued * kPairPitch + 64 + lane] = w1;
-        if (lane == j) {  // lane j holds the Gaussian's id
-          Rg[queued] = my_id;
-          Rc[queued] = c;
-        }
-        pix0 |= m0;
-        pix1 |= m1;
-        if (++queued == 32) {
-          flush(32);
-          queued = 0;
-          pix0 = pix1 = 0ull;
-        }
+      if ((hits0 >> j) & 1ull) w0 = blend_step(a, b, pxo0, pyo, T0);
+      if ((hits1 >> j) & 1ull) w1 = blend_step(a, b, pxo1, pyo, T1);
+      const uint64_t m0 = nonzero(w0), m1 = nonzero(w1);
+      const uint32_t c = (uint32_t)(__popcll(m0) + __popcll(m1));
+      Wt[queued * kPairPitch + lane] = w0;
+      Wt[queued * kPairPitch + 64 + lane] = w1;
+      Rg[queued] = (uint32_t)__builtin_amdgcn_readlane((int)my_id, j);  // every lane the same
+      Rc[queued] = c;
+      ncontrib += c;
+      pix0 |= m0;
+      pix1 |= m1;
+      queued += (m0 | m1) != 0ull ? 1 : 0;
+      if (queued == 32) {
+        flush(32);
+        queued = 0;
+        pix0 = pix1 = 0ull;
       }
     }
   }
@@ -1080,11 +1170,12 @@ __global__ __launch_bounds__(64, 2) void blend_pair_kernel(
 
 template <lv_dtype DT, bool PX>
 hipError_t launch_blend_t(const BlendArgs& a, int m, hipStream_t s) {
-  // one group: one wave per (view, quadrant, group); several: one wave per
-  // (view, quadrant) for all groups, sharing the walk
+  // one group: one workgroup per (view, quadrant); several: one wave per
+  // (view, half tile) for all groups, sharing the walk
   const bool multi = a.ngroups > 1;
-  int64_t work = (int64_t)a.tiles_stride * m * (multi ? 1 : a.ngroups);
+  int64_t work = (int64_t)a.tiles_stride * m;
   int64_t blocks = (work + 7) / 8 * 32;
+  const bool two = a.max_width > 0 || 4 * work <= kFewQuadrants;
   if (multi) {
     // one wave per half tile: two per tile, whole rounds of 8 XCDs
     const int64_t pblocks = ((int64_t)a.tiles_stride * m + 7) / 8 * 16;
@@ -1093,45 +1184,63 @@ hipError_t launch_blend_t(const BlendArgs& a, int m, hipStream_t s) {
                        a.ids, a.ranges, a.geom, a.n, a.tiles_stride, m, a.sets, a.groups,
                        a.ngroups);
   } else
-    hipLaunchKernelGGL((blend_wide_kernel<DT, PX>), dim3((unsigned)blocks), dim3(64), 0, s,
-                       a.rec, a.ids, a.ranges, a.geom, a.n, a.tiles_stride, m, a.sets, a.groups,
-                       a.ngroups);
+    hipLaunchKernelGGL((two ? blend_wide_kernel<DT, PX, true> : blend_wide_kernel<DT, PX, false>),
+                       dim3((unsigned)blocks), dim3(two ? 128 : 64), 0, s, a.rec, a.ids, a.ranges, a.geom, a.n,
+                       a.tiles_stride, m, a.sets, a.groups, a.ngroups);
   return hipGetLastError();
 }
 
 // ------------------------------------------------------------ forward render
-// Eq. (4): F^(p) = sum_i w_i(p) g_i, the adjoint of the uplift.  One wave per
-// (view, quadrant, group of 32 NB channels) walks its tile's list exactly as
-// the uplift does; a Gaussian with some contribution queues its weights at
-// the 64 pixels in one of 32 LDS rows (its index beside it).  A full queue
-// (and the last, partial one) is flushed on the matrix cores: out (64 pixels
-// x 32 NB channels) += W^T (64 x 32 rows) G (32 rows x 32 NB channels), split
-// BF16 operands as in the uplift, the 2 x NB 32x32 output blocks held in
-// registers until the walk ends; each (pixel, channel) is then written once.
-// The opacity sum_i w_i(p) goes to alpha[v] (group 0).  NB = 2 (64 channels)
-// for D <= 64, else 4: the walk, repeated for every group of channels, runs
-// half as often, and the 8 output blocks' 128 registers leave 2 waves per
-// SIMD instead of 3.
+// Eq. (4): F^(p) = sum_i w_i(p) g_i, the adjoint of the uplift.  One workgroup
+// per (view, quadrant) and one or three groups of 32 NB channels walks the
+// tile's list as the uplift does and, for each queue of up to 32 LDS rows, adds
+// out (64 pixels x 32 NB channels) += W^T (64 x 32 rows) G (32 rows x 32 NB
+// channels) on the matrix cores, split BF16 operands as in the uplift, the
+// 2 x NB 32x32 output blocks held in registers until the walk ends; each (pixel,
+// channel) is then written once.  The opacity sum_i w_i(p) goes to alpha[v]
+// (group 0).  NB = 1 for D <= 32, 2 for D <= 64, else 4 (128 registers of output
+// blocks, two waves per SIMD).
+// The walk is a serial chain, the products wait for rows of g.  kSplit: the
+// first wave walks and fills two queues in turn, each other wave takes a group
+// of channels and the queue just filled; else one wave does both for its group.
+// Split where the launch has few quadrants (half of kFewQuadrants at NB = 4,
+// whose registers leave room for two waves a SIMD: D = 128, 1536 quadrants, 91
+// us as one wave / 79 split; 3072: 75 / 88) and where the groups are a multiple
+// of three, which share one walk: 6 views of 1008x756, 1M Gaussians, D = 384,
+// 3.64 ms as three workgroups / 3.46 sharing; 8 views of 512x384, D = 257, 1.59
+// / 1.39, D = 384 1.28 / 1.31.  Two groups sharing a walk lose (D = 256: 0.88 /
+// 1.14 ms), and so does a last workgroup with idle waves (D = 385: 2.16 / 2.79).
+// Before the walk of blend_step, one wave per group: D = 384 as above 3.99 ms, 4
+// views of 512x384 with D = 3 155 us, now 136.
 // kVec: D is a multiple of NB and g and the outputs are aligned to NB floats;
 // a lane's channels are then consecutive (channel NB (l % 32) + b in block b),
 // and each row of g and each output pixel is one load or store of NB floats
-// instead of NB.  Else block b's channels are 32 b + l % 32.
-template <int NB, bool kVec>
-__global__ __launch_bounds__(64, (NB == 1 ? 4 : NB == 2 ? 3 : 2)) void render_kernel(
+// instead of NB (4.89 -> 3.99 ms on the first job above).  Else block b's
+// channels are 32 b + l % 32.
+constexpr int kRenderWaves = 3;  // channel groups that share a walk
+
+template <int NB, bool kVec, bool kSplit>
+__global__ __launch_bounds__(kSplit ? 64 * (1 + (NB == 4 ? kRenderWaves : 1)) : 64,
+                             (NB == 1 ? 4 : NB == 2 ? 3 : 2)) void render_kernel(
     const Rec* __restrict__ rec, const uint32_t* __restrict__ ids, const uint2* __restrict__ ranges,
-    const ViewGeom* __restrict__ geom, int64_t n, int tiles_stride, int nviews, int ngroups,
+    const ViewGeom* __restrict__ geom, int64_t n, int tiles_stride, int nviews, int nwork,
     const float* __restrict__ g, int D, float* const* __restrict__ outs,
     float* const* __restrict__ alphas, const uint32_t* __restrict__ perm) {
-  constexpr int G = kChunk;
-  __shared__ __align__(16) float Wt[32 * kWtPitch];  // queued Gaussians: [row][pixel]
-  __shared__ float4 Rs[kChunk][2];                   // the step's records
-  __shared__ uint32_t Rg[32];                        // queued Gaussians' ids
+  constexpr int kQueues = kSplit ? 2 : 1;
+  __shared__ __align__(16) float Wts[kQueues][32 * kWtPitch];  // queued Gaussians: [row][pixel]
+  __shared__ float4 Rs[kChunk][2];                             // the step's records
+  __shared__ int Count[kQueues];                               // rows, + 64 with the last ones
+  constexpr int kIds = kSplit ? 256 : 128;
+  __shared__ uint32_t Ids[kIds];  // the rows' Gaussians in order, row k at k mod kIds
   Quad q;
   // every in-image (pixel, channel) of every view is written, zeros where no
   // Gaussian reaches (a tile without Gaussians walks nothing)
-  if (!decode_quad(ranges, geom, tiles_stride, nviews, ngroups, q, true)) return;
-  const int lane = threadIdx.x;
-  const int c0 = q.cg * 32 * NB;
+  if (!decode_quad(ranges, geom, tiles_stride, nviews, nwork, q, true)) return;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int px = q.qx + (lane & 7), py = q.qy + (lane >> 3);
+
+  const int c0 = (kSplit ? q.cg * ((int)(blockDim.x >> 6) - 1) + wave - 1 : q.cg) * 32 * NB;
   // this lane's channel in each 32-channel block (a readable one where it has none)
   int ch[NB];
   bool own[NB];
@@ -1145,24 +1254,21 @@ __global__ __launch_bounds__(64, (NB == 1 ? 4 : NB == 2 ? 3 : 2)) void render_ke
   f32x16 acc[2][NB];  // [pixel block][channel block]
 #pragma unroll
   for (int b = 0; b < NB; b++) acc[0][b] = acc[1][b] = f32x16{};
-  float asum = 0.0f;
-  int queued = 0;
 
-  // K-step t: queue rows 16 t + 8 (l / 32) + i, i < 8.  Rows past count
-  // have weight 0 and read the features of row 0 (in this flush), and a lane
-  // without a channel feeds only its own output column, never written: the
-  // loaded features are used as loaded (no select, so no zero fill that would
-  // wait for every load in flight).
-  auto flush = [&](int count) {
-    __syncthreads();  // rows written (one wave per workgroup: orders LDS)
-    for (int t = 0; t < 2 && 16 * t < count; t++) {
+  auto flush = [&](const float* Wt, int count, uint32_t row0) {
+    // K-step t: queue rows 16 t + 8 (l / 32) + i, i < 8.  Rows past count
+    // have weight 0 and read the features of row 0 (in this queue), and a lane
+    // without a channel feeds only its own output column, never written: the
+    // loaded features are used as loaded (no select, so no zero fill that would
+    // wait for every load in flight).
+    for (int t = 0; t < 2 && 16 * t < count && c0 < D; t++) {
       float w0[8], w1[8];
       int64_t gid[8];
 #pragma unroll
       for (int i = 0; i < 8; i++) {
         const int row = 16 * t + 8 * (lane >> 5) + i;
         const bool ok = row < count;
-        gid[i] = (int64_t)Rg[ok ? row : 0];
+        gid[i] = (int64_t)Ids[(row0 + (uint32_t)(ok ? row : 0)) % kIds];
         w0[i] = ok ? Wt[row * kWtPitch + (lane & 31)] : 0.0f;
         w1[i] = ok ? Wt[row * kWtPitch + 32 + (lane & 31)] : 0.0f;
       }
@@ -1196,47 +1302,96 @@ __global__ __launch_bounds__(64, (NB == 1 ? 4 : NB == 2 ? 3 : 2)) void render_ke
         acc[1][c] = mfma(a1h, bl, acc[1][c]);
       }
     }
-    __syncthreads();  // rows read before they are written again
   };
 
-  Walk s;
-  walk_init(q, lane, s);
-  const Rec* vrec = rec + (int64_t)q.v * n;
-  for (uint32_t base = q.rg.x; base < q.rg.y; base += G) {
-    if (__ballot(s.alive) == 0ull) break;
-    const int cnt = (int)(q.rg.y - base < (uint32_t)G ? q.rg.y - base : (uint32_t)G);
-    uint32_t my_id;
-    const uint64_t hits = step_records(vrec, ids, base, cnt, lane, s, my_id, Rs, perm);
-    if (!hits) continue;
-    __syncthreads();  // records in LDS (one wave per workgroup: orders LDS)
-    for (uint64_t h = hits; h; h &= h - 1) {
-      const int j = (int)__builtin_ctzll(h);
-      bool take;
-      const float wj = walk_rec(Rs[j][0], Rs[j][1], s, take);
-      if (__ballot(take)) {
-        Wt[queued * kWtPitch + lane] = wj;
-        if (lane == j) Rg[queued] = my_id;  // lane j holds the Gaussian's (caller) index
-        asum += wj;
-        if (++queued == 32) {
-          flush(32);
-          queued = 0;
-        }
+  if (wave == 0) {
+    Walk s;
+    walk_init(q, lane, s);
+    Steps<kSplit> st;
+    if (q.rg.y > q.rg.x) st.start(rec + (int64_t)q.v * n, ids, q.rg, lane, perm);
+    int b = 0, queued = 0;   // rows [0, queued) of queue b hold Gaussians
+    uint32_t rows_done = 0u; // rows whose ids are in Ids
+    uint64_t kept = 0ull;    // hits of the step that took a row since
+    uint32_t my_id = 0u;
+    float asum = 0.0f;
+    uint32_t row0 = 0u;      // the queue's first row
+    float* wrow = Wts[0] + lane;
+    auto write_ids = [&]() {
+      if ((kept >> lane) & 1ull)
+        Ids[(rows_done + (uint32_t)__popcll(kept & ((1ull << lane) - 1ull))) % kIds] = my_id;
+      rows_done += (uint32_t)__popcll(kept);
+      kept = 0ull;
+    };
+    auto hand_over = [&](int count) {
+      write_ids();
+      if constexpr (kSplit) {
+        if (lane == 0) Count[b] = count;
+        lds_barrier();
+        b ^= 1;
+      } else {
+        lds_order();
+        flush(Wts[0], count & 63, row0);
+        lds_order();
+        row0 += 32u;
       }
+      queued = 0;
+      wrow = Wts[b] + lane;
+    };
+    for (uint32_t base = q.rg.x; base < q.rg.y; base += kChunk) {
+      if (nonzero(s.T) == 0ull) break;
+      uint64_t h = step_records(st, base, lane, s, my_id, Rs);
+      if (!h) continue;
+      lds_order();  // records in LDS
+      int j = (int)__builtin_ctzll(h);
+      float4 ra = Rs[j][0];
+      float2 rb = *reinterpret_cast<const float2*>(&Rs[j][1]);
+      do {
+        const uint64_t bit = 1ull << j;
+        h &= ~bit;
+        j = (int)__builtin_ctzll(h | (1ull << 63));  // 63 after the last: a readable record
+        const float4 ca = ra;
+        const float2 cb = rb;
+        ra = Rs[j][0];
+        rb = *reinterpret_cast<const float2*>(&Rs[j][1]);
+        const float wj = blend_step(ca, cb, s.pxo, s.pyo, s.T);
+        *wrow = wj;
+        asum += wj;
+        if (nonzero(wj)) {  // else the next hit takes the row: a row costs 32 NB channels of g
+          kept |= bit;
+          wrow += kWtPitch;
+          if (++queued == 32) hand_over(32);
+        }
+      } while (h);
+      write_ids();
+      lds_order();  // the records are read before the next step's
+    }
+    hand_over(queued + 64);
+    if (q.cg == 0 && alphas[q.v] && px < q.g.W && py < q.g.H)
+      gptr(alphas[q.v])[(int64_t)py * q.g.W + px] = asum;
+    if (kSplit) return;
+  }
+  if constexpr (kSplit) {
+    uint32_t row0 = 0u;  // the queue's first row
+    for (int b = 0;; b ^= 1) {
+      lds_barrier();
+      const int handed = __builtin_amdgcn_readfirstlane(Count[b]);
+      flush(Wts[b], handed & 63, row0);
+      row0 += 32u;
+      if (handed & 64) break;
     }
   }
-  if (queued > 0) flush(queued);
 
   // D row m of a block: pixel 32 pb + 8 (r / 4) + 4 (l / 32) + r % 4, column
-  // (channel) l % 32
+  // l % 32
   float* const out = outs[q.v];
 #pragma unroll
   for (int pb = 0; pb < 2; pb++) {
 #pragma unroll
     for (int r = 0; r < 16; r++) {
       const int m = 32 * pb + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-      const int px = q.qx + (m & 7), py = q.qy + (m >> 3);
-      if (px < q.g.W && py < q.g.H) {
-        const int64_t pix = (int64_t)py * q.g.W + px;
+      const int ox = q.qx + (m & 7), oy = q.qy + (m >> 3);
+      if (ox < q.g.W && oy < q.g.H) {
+        const int64_t pix = (int64_t)oy * q.g.W + ox;
         if constexpr (kVec && NB > 1) {
           fvec o;
 #pragma unroll
@@ -1250,9 +1405,6 @@ __global__ __launch_bounds__(64, (NB == 1 ? 4 : NB == 2 ? 3 : 2)) void render_ke
       }
     }
   }
-  const int px = q.qx + (lane & 7), py = q.qy + (lane >> 3);
-  if (q.cg == 0 && alphas[q.v] && px < q.g.W && py < q.g.H)
-    gptr(alphas[q.v])[(int64_t)py * q.g.W + px] = asum;
 }
 
 // D a multiple of 4, 16-byte aligned arrays: a block takes 64 Gaussians,
@@ -1354,14 +1506,19 @@ hipError_t launch_render(const BlendArgs& a, int m, const float* g, int D, float
   if (m == 0 || a.tiles_stride == 0) return hipSuccess;
   const int nb = D > 64 ? 4 : D > 32 ? 2 : 1;  // 32-channel blocks per wave
   const int ngroups = (D + 32 * nb - 1) / (32 * nb);
-  const int64_t work = (int64_t)a.tiles_stride * m * ngroups;
+  const int waves = ngroups % kRenderWaves == 0 ? kRenderWaves : 1;  // groups per workgroup
+  const int nwork = ngroups / waves;                                 // workgroups per quadrant
+  const bool split = waves > 1 || (int64_t)a.tiles_stride * m * nwork * 4 <= kFewQuadrants / (nb == 4 ? 2 : 1);
+  const int64_t work = (int64_t)a.tiles_stride * m * nwork;
   const int64_t blocks = (work + 7) / 8 * 32;  // 4 quadrants per tile, whole rounds of 8 XCDs
   const bool vec = D % nb == 0 && (uintptr_t)g % (4 * nb) == 0 && outs_align % (4 * nb) == 0;
-  const auto kernel = nb == 1   ? render_kernel<1, false>
-                      : nb == 2 ? (vec ? render_kernel<2, true> : render_kernel<2, false>)
-                                : (vec ? render_kernel<4, true> : render_kernel<4, false>);
-  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64), 0, s, a.rec, a.ids, a.ranges, a.geom, a.n,
-                     a.tiles_stride, m, ngroups, g, D, outs, alphas, perm);
+  const auto kernel = nb == 1   ? (split ? render_kernel<1, false, true> : render_kernel<1, false, false>)
+                      : nb == 2 ? (vec ? (split ? render_kernel<2, true, true> : render_kernel<2, true, false>)
+                                       : (split ? render_kernel<2, false, true> : render_kernel<2, false, false>))
+                                : (vec ? (split ? render_kernel<4, true, true> : render_kernel<4, true, false>)
+                                       : (split ? render_kernel<4, false, true> : render_kernel<4, false, false>));
+  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(split ? 64 * (1 + waves) : 64), 0, s, a.rec, a.ids,
+                     a.ranges, a.geom, a.n, a.tiles_stride, m, nwork, g, D, outs, alphas, perm);
   return hipGetLastError();
 }
 

@@ -251,7 +251,7 @@ struct BlendArgs {
   const SetDesc* sets;         // device
   const ChanGroup* groups;     // device (wide kernel)
   int32_t ngroups;
-  int32_t max_width;           // widest group (LDS size)
+  int32_t max_width;           // widest group; 0: tail channels only
   int32_t has_tail;            // the last group has tail channels
 };
 hipError_t launch_blend(const BlendArgs& a, lv_dtype dtype, int m, hipStream_t s);
