@@ -296,101 +296,188 @@ __global__ __launch_bounds__(256) void spmm_rows_kernel(const int32_t* __restric
   }
 }
 
-// Four consecutive channels per lane (D = 4 L, L lanes per row, 64 / L rows
-// per wave): the gathers are 16-byte (FP32) or 8-byte (BF16) loads of a
-// neighbour's channels and a wave keeps several rows in flight.  A row's
-// edges are fetched L at a time, one per lane, and broadcast with shuffles;
-// 8 gathers in flight per lane.  Sums in edge order, as spmm_kernel.
-template <int L, lv_dtype GT, lv_dtype VT>
-__global__ __launch_bounds__(256) void spmm4_kernel(const int32_t* __restrict__ row_ptr,
-                                                    const int32_t* __restrict__ col,
-                                                    const void* __restrict__ val, int64_t n,
-                                                    const void* __restrict__ g,
-                                                    const float* __restrict__ nrm_in, int slots,
-                                                    void* __restrict__ y, float* __restrict__ nrm_out) {
-  constexpr int D = 4 * L, R = 64 / L, U = 8;
-  __shared__ float sq[256 * 4];
-  const int t = threadIdx.x, lane = t & 63;
-  const int sub = lane / L, c4 = lane % L, gbase = sub * L;
-  float scl[4], ss[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  {
-    const float v = slot_sum<D>(nrm_in, slots, D, t & (D - 1), sq);
-    if (t < D) sq[t] = v;
-    __syncthreads();
-  }
+// D = 8, 16, 32 or 64 channels in rows of 16-byte pieces: C channels per lane (4
+// in FP32, 8 in BF16: one 16-byte load), L = D / C lanes per row, R = 64 / L
+// consecutive rows per wave, whose edges are one contiguous range.  The wave
+// takes that range E edges at a time: columns and weights are read coalesced and
+// left in LDS as (row offset, weight); each row's lanes then walk the row's part,
+// U gathers in flight, and sum in edge order with the same fused multiply-adds as
+// spmm_kernel.
+// What bounds a step is instructions and latency before bandwidth: with four
+// channels per lane, edges broadcast by shuffles and a block per 16 rows, each
+// gather cost a BF16 lane 13 instructions for 4 channels (now about 18 for 8), and
+// every block began with the norms, the row pointers and the edges one after the
+// other.  The blocks now stay (kSpmmWideBlocks), and a tile's edges and the next
+// one's row pointers are loaded while the tile before is summed.  U = 4: of 4, 6,
+// 8 and 12 gathers in flight 4 is the fastest or level everywhere (D = 64 in
+// FP32, 1M rows: 252, 269, 272, 303 us a step).  Steps, 16 edges a row, before and
+// now: 1M rows, D = 64, BF16 207 -> 144 us (338 MB: 2.3 TB/s), FP32 260 -> 252;
+// 300k rows, D = 32, BF16 50 -> 29, D = 16 30 -> 21, D = 8 28 -> 17; 5,000 rows,
+// D = 16 11.2 -> 9.8, D = 64 11.3 -> 12.1 (half as many waves there).
+// kBig: offsets of g do not fit 32 bits (else they are formed when staged, and a
+// gather is one addition and one load).
+template <int D, lv_dtype GT, lv_dtype VT, bool kBig>
+__global__ __launch_bounds__(256) void spmm_wide_kernel(const int32_t* __restrict__ row_ptr,
+                                                        const int32_t* __restrict__ col,
+                                                        const void* __restrict__ val, int64_t n,
+                                                        const void* __restrict__ g,
+                                                        const float* __restrict__ nrm_in, int slots,
+                                                        void* __restrict__ y, float* __restrict__ nrm_out) {
+  constexpr int C = GT == LV_F32 ? 4 : 8, L = D / C, R = 64 / L, U = 4;
+  constexpr int E = R > 32 ? 16 * R : 512, P = R < 32 ? 4 : 8;  // edges per round, per lane and load
+  constexpr uint32_t kRowBytes = D * (GT == LV_F32 ? 4 : 2);
+  __shared__ union {
+    uint2 edge[4][E];
+    float sq[256 * C];
+  } sh;
+  __shared__ float scales[D];
+  const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int sub = lane / L, cl = lane % L;
+  uint2* const edge = sh.edge[wv];
+  const char* const gb = static_cast<const char*>(g);
+  // a gathered row's piece of this lane
+  const auto gather = [&](uint32_t off) {
+    if constexpr (kBig)
+      return *reinterpret_cast<const uint4*>(gb + (uint64_t)off * kRowBytes + 16 * cl);
+    else
+      return *reinterpret_cast<const uint4*>(gb + (off + 16u * (uint32_t)cl));
+  };
+  const auto add = [&](float (&acc)[C], float w, const uint4& q) {
+    const uint32_t r[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
-  for (int k = 0; k < 4; k++) {
-    const float n2 = sq[4 * c4 + k];
-    scl[k] = n2 > 0.0f ? 1.0f / sqrtf(n2) : 0.0f;
-  }
+    for (int k = 0; k < 4; k++) {
+      if constexpr (GT == LV_F32) {
+        acc[k] = __builtin_fmaf(w, __uint_as_float(r[k]), acc[k]);
+      } else {
+        acc[2 * k] = __builtin_fmaf(w, __uint_as_float(r[k] << 16), acc[2 * k]);
+        acc[2 * k + 1] = __builtin_fmaf(w, __uint_as_float(r[k] & 0xFFFF0000u), acc[2 * k + 1]);
+      }
+    }
+  };
+  // XCD x (= blockIdx mod 8) takes the x-th eighth of the rows (locality order)
   const int64_t tiles = (n + 4 * R - 1) / (4 * R);
   const int64_t xcd = blockIdx.x & 7, nloc = gridDim.x >> 3;
   const int64_t t0 = tiles * xcd / 8, t1 = tiles * (xcd + 1) / 8;
-  for (int64_t tile = t0 + (blockIdx.x >> 3); tile < t1; tile += nloc) {
-    const int64_t row = (tile * 4 + (t >> 6)) * R + sub;
-    const bool valid = row < n;
-    const int32_t a = valid ? row_ptr[row] : 0, b = valid ? row_ptr[row + 1] : 0;
-    float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int32_t e0 = a; e0 < b; e0 += L) {
-      const int32_t my = e0 + c4;
-      const int32_t cv = my < b ? col[my] : 0;
-      const float wv = my < b ? ld<VT>(val, my) : 0.0f;
-      const int cnt = b - e0 < L ? b - e0 : L;
-      for (int j = 0; j < cnt; j += U) {
-        float w[U], x[U][4];
+  // this lane's row of a tile (its edges [a, b)), and 64 P edges of a wave
+  const auto load_rows = [&](int64_t tile, int32_t& a, int32_t& b) {
+    const int64_t row = (tile * 4 + wv) * R + sub;
+    a = row_ptr[tile < t1 && row < n ? row : n];
+    b = row_ptr[tile < t1 && row < n ? row + 1 : n];
+  };
+  uint32_t cj[P];
+  float w[P];
+  const auto load_edges = [&](int32_t e0, int32_t m) {  // m > 0 edges from e0; past them the last again
+#pragma unroll
+    for (int u = 0; u < P; u++) {
+      const int32_t q = 64 * u + lane;
+      const int32_t e = e0 + (q < m ? q : m - 1);
+      cj[u] = (uint32_t)col[e];
+      w[u] = ld<VT>(val, e);
+    }
+  };
+  int64_t tile = t0 + (blockIdx.x >> 3);
+  int32_t a, b, an, bn;  // this tile's row and the next's
+  load_rows(tile, a, b);
+  load_rows(tile + nloc, an, bn);
+  int32_t first = __builtin_amdgcn_readlane(a, 0), last = __builtin_amdgcn_readlane(b, 63);
+  if (first < last) load_edges(first, last - first);
+  {
+    const float n2 = slot_sum<D>(nrm_in, slots, D, t & (D - 1), sh.sq);
+    if (t < D) scales[t] = n2 > 0.0f ? 1.0f / sqrtf(n2) : 0.0f;
+    __syncthreads();
+  }
+  float ss[C] = {};
+  for (; tile < t1; tile += nloc) {
+    const int64_t row = (tile * 4 + wv) * R + sub;
+    float acc[C] = {};
+    int32_t base = first;
+    do {
+      const int32_t m = last - base < E ? last - base : E;  // edges of this round
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the last round's are read
+      __builtin_amdgcn_wave_barrier();
+      for (int32_t q0 = 0; q0 < m; q0 += 64 * P) {
+        if (base + q0 > first) load_edges(base + q0, m - q0);
+#pragma unroll
+        for (int u = 0; u < P; u++)
+          edge[q0 + 64 * u + lane] = make_uint2(kBig ? cj[u] : cj[u] * kRowBytes, __float_as_uint(w[u]));
+      }
+      if (base + m == last) {  // the next tile's first edges
+        const int32_t e0 = __builtin_amdgcn_readlane(an, 0), e1 = __builtin_amdgcn_readlane(bn, 63);
+        if (e0 < e1) load_edges(e0, e1 - e0);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      int32_t j = a > base ? a - base : 0;
+      const int32_t j1 = b - base < m ? b - base : m;
+      for (; j + U <= j1; j += U) {
+        uint2 ed[U];
+        uint4 x[U];
 #pragma unroll
         for (int u = 0; u < U; u++) {
-          const int src = gbase + ((j + u) < L ? (j + u) : 0);
-          const int32_t cj = __shfl(cv, src, 64);
-          const float wj = __shfl(wv, src, 64);
-          w[u] = (j + u) < cnt ? wj : 0.0f;
-          const int64_t off = (int64_t)cj * D + 4 * c4;
-          if constexpr (GT == LV_F32) {
-            const float4 q = *reinterpret_cast<const float4*>(static_cast<const float*>(g) + off);
-            x[u][0] = q.x;
-            x[u][1] = q.y;
-            x[u][2] = q.z;
-            x[u][3] = q.w;
-          } else {
-            const uint2 q = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(g) + off);
-            x[u][0] = __uint_as_float(q.x << 16);
-            x[u][1] = __uint_as_float(q.x & 0xFFFF0000u);
-            x[u][2] = __uint_as_float(q.y << 16);
-            x[u][3] = __uint_as_float(q.y & 0xFFFF0000u);
-          }
+          ed[u] = edge[j + u];
+          x[u] = gather(ed[u].x);
         }
 #pragma unroll
-        for (int u = 0; u < U; u++)
-#pragma unroll
-          for (int k = 0; k < 4; k++) acc[k] = __builtin_fmaf(w[u], x[u][k], acc[k]);
+        for (int u = 0; u < U; u++) add(acc, __uint_as_float(ed[u].y), x[u]);
       }
-    }
-    if (valid) {
-      float o[4];
+      if (j < j1) {  // fewer than U left: the last edge's row again, taken as zeros
+        uint2 ed[U];
+        uint4 x[U];
 #pragma unroll
-      for (int k = 0; k < 4; k++) {
-        o[k] = stored<GT>(scl[k] * acc[k]);
+        for (int u = 0; u < U; u++) {
+          ed[u] = edge[j + u < j1 ? j + u : j1 - 1];
+          x[u] = gather(ed[u].x);
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+          const bool ok = j + u < j1;
+          const uint4 z = make_uint4(ok ? x[u].x : 0u, ok ? x[u].y : 0u, ok ? x[u].z : 0u, ok ? x[u].w : 0u);
+          add(acc, ok ? __uint_as_float(ed[u].y) : 0.0f, z);
+        }
+      }
+      base += m;
+    } while (base < last);
+    a = an;
+    b = bn;
+    first = __builtin_amdgcn_readlane(a, 0);
+    last = __builtin_amdgcn_readlane(b, 63);
+    load_rows(tile + 2 * nloc, an, bn);
+    if (row < n) {
+      float o[C];
+#pragma unroll
+      for (int k = 0; k < C; k++) {
+        o[k] = stored<GT>(scales[C * cl + k] * acc[k]);  // the norm of what is stored
         ss[k] = __builtin_fmaf(o[k], o[k], ss[k]);
       }
-      const int64_t off = row * D + 4 * c4;
+      uint4 q;
       if constexpr (GT == LV_F32) {
-        *reinterpret_cast<float4*>(static_cast<float*>(y) + off) = make_float4(o[0], o[1], o[2], o[3]);
+        q = make_uint4(__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3]));
       } else {
-        const uint2 q = make_uint2((__float_as_uint(o[0]) >> 16) | (__float_as_uint(o[1]) & 0xFFFF0000u),
-                                   (__float_as_uint(o[2]) >> 16) | (__float_as_uint(o[3]) & 0xFFFF0000u));
-        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(y) + off) = q;
+        const auto pack = [&](int k) { return (__float_as_uint(o[k]) >> 16) | __float_as_uint(o[k + 1]); };
+        q = make_uint4(pack(0), pack(2), pack(4), pack(6));
       }
+      *reinterpret_cast<uint4*>(static_cast<char*>(y) + row * (int64_t)kRowBytes + 16 * cl) = q;
     }
   }
-  __syncthreads();  // the norms in sq are read
-  // per-channel sums over the block: threads t = c4 (mod L) hold channels 4 c4 .. 4 c4 + 3
+  // per-channel sums over the block: threads t = cl (mod L) hold channels C cl ..
+  // C cl + C - 1.  Where many threads share a channel (L <= 4) the lanes of a wave
+  // are summed by shuffles first: 128 LDS reads in a row by few threads took 3 us
+  // of a 13 us step on 5,000 rows (D = 16).
+  constexpr bool kShfl = L <= 4;
+  if constexpr (kShfl) {
 #pragma unroll
-  for (int k = 0; k < 4; k++) sq[k * 256 + t] = ss[k];
+    for (int k = 0; k < C; k++)
+#pragma unroll
+      for (int off = L; off < 64; off <<= 1) ss[k] += __shfl_xor(ss[k], off, 64);
+  }
+  __syncthreads();  // the edges are read
+#pragma unroll
+  for (int k = 0; k < C; k++) sh.sq[k * 256 + t] = ss[k];
   __syncthreads();
   if (t < D) {
-    const int k = t & 3, cc = t >> 2;
+    const int k = t % C, cc = t / C;
     float s2 = 0.0f;
-    for (int q = cc; q < 256; q += L) s2 += sq[k * 256 + q];
+    for (int q = cc; q < 256; q += kShfl ? 64 : L) s2 += sh.sq[k * 256 + q];
     if (s2 != 0.0f) atomicAdd(&nrm_out[(int64_t)(blockIdx.x % (unsigned)slots) * D + t], s2);
   }
 }
@@ -416,16 +503,22 @@ hipError_t spmm_launch(const int32_t* rp, const int32_t* col, const void* val, i
   return hipGetLastError();
 }
 
-template <int L, lv_dtype GT, lv_dtype VT>
-hipError_t spmm4_launch(const int32_t* rp, const int32_t* col, const void* val, int64_t n,
-                        const void* g, const float* nin, int slots, void* y, float* nout,
-                        hipStream_t s) {
-  constexpr int R = 64 / L;
+// Five blocks per CU, all resident, sweep the rows in order: 1024, 1280, 1536 and
+// 2048 blocks take 162, 144, 138 and 172 us a step (1M rows, D = 64, 16 edges a
+// row, BF16) and 262, 252, 260 and 293 in FP32.
+constexpr int64_t kSpmmWideBlocks = 1280;
+
+template <int D, lv_dtype GT, lv_dtype VT>
+hipError_t spmm_wide_launch(const int32_t* rp, const int32_t* col, const void* val, int64_t n,
+                            const void* g, const float* nin, int slots, void* y, float* nout,
+                            hipStream_t s) {
+  constexpr int R = 64 * (GT == LV_F32 ? 4 : 8) / D;  // rows per wave
   const int64_t tiles = (n + 4 * R - 1) / (4 * R);
   const int64_t want = (tiles + 7) / 8 * 8;
-  const unsigned blocks = (unsigned)(want < 8192 ? want : 8192);
-  hipLaunchKernelGGL((spmm4_kernel<L, GT, VT>), dim3(blocks), dim3(256), 0, s, rp, col, val, n, g, nin,
-                     slots, y, nout);
+  const unsigned blocks = (unsigned)(want < kSpmmWideBlocks ? want : kSpmmWideBlocks);
+  const bool big = n * D * (GT == LV_F32 ? 4 : 2) > (int64_t)1 << 32;
+  hipLaunchKernelGGL((big ? spmm_wide_kernel<D, GT, VT, true> : spmm_wide_kernel<D, GT, VT, false>),
+                     dim3(blocks), dim3(256), 0, s, rp, col, val, n, g, nin, slots, y, nout);
   return hipGetLastError();
 }
 
@@ -449,13 +542,12 @@ hipError_t spmm_dispatch(const int32_t* rp, const int32_t* col, const void* val,
   if (D == 2) return spmm_rows_launch<2, GT, VT>(rp, col, val, n, g, nin, slots, y, nout, s);
   if (D == 3) return spmm_rows_launch<3, GT, VT>(rp, col, val, n, g, nin, slots, y, nout, s);
   if (D == 4) return spmm_rows_launch<4, GT, VT>(rp, col, val, n, g, nin, slots, y, nout, s);
-  // four channels per lane where D = 4 L, L = 2 .. 16 a power of two and the
-  // rows are 16-byte (FP32) or 8-byte (BF16) aligned
+  // 16-byte pieces of rows where the arrays are aligned to them
   if (((uintptr_t)g % 16 == 0) && ((uintptr_t)y % 16 == 0)) {
-    if (D == 64) return spmm4_launch<16, GT, VT>(rp, col, val, n, g, nin, slots, y, nout, s);
-    if (D == 32) return spmm4_launch<8, GT, VT>(rp, col, val, n, g, nin, slots, y, nout, s);
-    if (D == 16) return spmm4_launch<4, GT, VT>(rp, col, val, n, g, nin, slots, y, nout, s);
-    if (D == 8) return spmm4_launch<2, GT, VT>(rp, col, val, n, g, nin, slots, y, nout, s);
+    if (D == 64) return spmm_wide_launch<64, GT, VT>(rp, col, val, n, g, nin, slots, y, nout, s);
+    if (D == 32) return spmm_wide_launch<32, GT, VT>(rp, col, val, n, g, nin, slots, y, nout, s);
+    if (D == 16) return spmm_wide_launch<16, GT, VT>(rp, col, val, n, g, nin, slots, y, nout, s);
+    if (D == 8) return spmm_wide_launch<8, GT, VT>(rp, col, val, n, g, nin, slots, y, nout, s);
   }
   if (D >= 64) return spmm_launch<64, GT, VT>(rp, col, val, n, D, g, nin, slots, y, nout, s);
   if (D > 16) return spmm_launch<32, GT, VT>(rp, col, val, n, D, g, nin, slots, y, nout, s);

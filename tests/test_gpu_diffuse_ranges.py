@@ -43,3 +43,23 @@ def test_diffuse_edges(D, n, vdt):
     out = G.diffuse(torch.as_tensor(g0, device="cuda"), steps).cpu().numpy().astype(np.float64)
     ref = od.diffuse(od.csr_matrix(n, rp, col, val), g0.astype(np.float64), steps)
     assert np.all(np.abs(out - ref) <= steps * (hub + 70) * 2.0 ** -24 * np.abs(ref))
+
+
+@pytest.mark.parametrize("sdt", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [1, 33, 129, 4097])
+@pytest.mark.parametrize("D", [8, 16, 32, 64])
+def test_diffuse_pieces_of_rows(D, n, sdt):
+    # signals in rows of 16-byte pieces, FP32 and BF16; a hub longer than two
+    # staging rounds.  One step; BF16: the signal rounded once (2^-9) before the
+    # last bounds
+    hub = 2500
+    rp, col, val = ragged_graph(n, 11 * n + D, hub)
+    g0 = torch.as_tensor(np.random.default_rng(n + D).uniform(0.1, 1.0, (n, D)).astype(np.float32))
+    if sdt == "bf16":
+        g0 = g0.to(torch.bfloat16)
+    G = lv.Graph(*(torch.as_tensor(x, device="cuda") for x in (rp, col, val)))
+    print(f"diffuse n={n} D={D} {sdt}", flush=True)
+    out = G.diffuse(g0.cuda(), 1).float().cpu().numpy().astype(np.float64)
+    ref = od.diffuse(od.csr_matrix(n, rp, col, val), g0.float().numpy().astype(np.float64), 1)
+    tol = (hub + 70) * 2.0 ** -24 + (2.0 ** -8 if sdt == "bf16" else 0.0)
+    assert np.all(np.abs(out - ref) <= tol * np.abs(ref))
