@@ -566,12 +566,14 @@ __device__ __forceinline__ void batch_scatter(const GroupLanes& L, bool two, int
 // walks and fills two queues of 32 rows in turn, the second flushes the one just
 // filled, and they meet at one barrier per queue, which neither loads nor atomics
 // in flight hold up; else one wave does both with one queue.  Two waves where
-// the launch has few quadrants (kFewQuadrants) or the group has a matrix block,
-// whose flush is long.  Launch, the walk before blend_step / one wave / two: 200k
-// Gaussians, 50 views of 512x384, D = 64 in BF16 3.57 / 3.52 / 3.42 ms (the
-// atomics' rate bounds it), D = 1 1.84 / 1.45 / 1.94; 10k Gaussians, 4 views of
-// 128x128, D = 8 165 / 133 / 82 us; 50k Gaussians, nine launches of a 333x251
-// view, D = 37 455 / 445 / 390 us.  Occupancy: waves per SIMD the register
+// the launch has few quadrants (kFewQuadrants) or the group more than 32
+// channels, whose flush is long.  Launch, the walk before blend_step / one wave /
+// two: 200k Gaussians, 50 views of 512x384, D = 64 in BF16 3.57 / 3.52 / 3.42 ms
+// (the atomics' rate bounds it), D = 1 1.84 / 1.45 / 1.94; 20 views, D = 32 in
+// FP32 1.04 / 0.98 / 0.96, in BF16 1.05 / 1.02 / 0.92; 20k Gaussians, 20 views of
+// 800x600, D = 32 in FP32 0.99 / 0.88 / 1.08, D = 16 0.95 / 0.83 / 1.03; 10k
+// Gaussians, 4 views of 128x128, D = 8 165 / 133 / 82 us; 50k Gaussians, nine
+// launches of a 333x251 view, D = 37 455 / 445 / 390 us.  Occupancy: waves per SIMD the register
 // allocation must allow.  BF16 maps need no low operand halves, so they fit four.
 template <lv_dtype DT>
 constexpr int wide_waves() {
@@ -1175,7 +1177,7 @@ hipError_t launch_blend_t(const BlendArgs& a, int m, hipStream_t s) {
   const bool multi = a.ngroups > 1;
   int64_t work = (int64_t)a.tiles_stride * m;
   int64_t blocks = (work + 7) / 8 * 32;
-  const bool two = a.max_width > 0 || 4 * work <= kFewQuadrants;
+  const bool two = a.max_width > 32 || 4 * work <= kFewQuadrants;
   if (multi) {
     // one wave per half tile: two per tile, whole rounds of 8 XCDs
     const int64_t pblocks = ((int64_t)a.tiles_stride * m + 7) / 8 * 16;

@@ -1,5 +1,5 @@
 """The walk's kernels on both sides of their rules: few quadrants (two waves
-per quadrant) and more than 4096 (one, unless the group has a matrix block);
+per quadrant) and more than 4096 (one, unless the group has over 32 channels);
 channel counts at the edges of the tails, the 32-channel blocks and the groups
 of the uplift and the render, rendered groups that share a walk and that do
 not; tiles whose lists run over many steps and queues.  Reference: the FP64
