@@ -369,7 +369,7 @@ lv_status lv_graph_destroy(lv_graph* graph);
  * positive weight are stored, columns ascending; rows are normalised to sum
  * 1 (FP32 values) and a row without any gets a self-loop of weight 1.
  * feats: device FP32 [n][D] (e.g. uplifted features).  Scratch (about
- * 90 + 48 k bytes per Gaussian) comes from the stream-ordered allocator; the
+ * 90 + 48 k bytes per Gaussian) is the stream's, kept until lv_release_scratch; the
  * call synchronises the stream once (to size the CSR).  Errors:
  * LV_ERR_INVALID_ARG (k outside [1, 32], D outside [1, 4096], n <= k, null
  * pointers), LV_ERR_UNSUPPORTED (n (2k + 1) >= 2^31), LV_ERR_OUT_OF_MEMORY,
