@@ -520,11 +520,15 @@ __device__ __forceinline__ void batch_mfma(bool two, uint32_t rows, const float*
   }
 }
 
+// Rows [0, count) of a batch, count <= 32.
+__device__ __forceinline__ uint32_t first_rows(int count) { return count < 32 ? (1u << count) - 1u : ~0u; }
+
 // One atomic per (queued Gaussian, channel): D row m of the batch is ring
-// row m, whose Gaussian id lane m holds.  FP8 maps: the products were formed
-// on the codes, the channel's scale multiplies them here.
+// row m, whose Gaussian id lane m holds; live: the rows that are added.  FP8
+// maps: the products were formed on the codes, the channel's scale multiplies
+// them here.
 template <lv_dtype DT, bool FIX>
-__device__ __forceinline__ void batch_scatter_t(const GroupLanes& L, bool two, int count,
+__device__ __forceinline__ void batch_scatter_t(const GroupLanes& L, bool two, uint32_t live,
                                                 uint32_t ring_gid, int lane, f32x16 acc0,
                                                 f32x16 acc1) {
   if constexpr (DT == LV_FP8_E4M3) {
@@ -532,14 +536,15 @@ __device__ __forceinline__ void batch_scatter_t(const GroupLanes& L, bool two, i
     acc1 *= L.srcsc[1];
   }
   const bool upper = lane >= 32;
+  const uint32_t mine = upper ? live >> 4 : live;
 #pragma unroll
   for (int r = 0; r < 16; r++) {
     const int m0 = 8 * (r >> 2) + (r & 3), m1 = m0 + 4;
-    if (m0 < count) {
+    if ((live >> m0) & 0x11u) {  // wave-uniform
       const uint32_t g0 = (uint32_t)__builtin_amdgcn_readlane((int)ring_gid, m0);
       const uint32_t g1 = (uint32_t)__builtin_amdgcn_readlane((int)ring_gid, m1);
       const int64_t gid = (int64_t)(upper ? g1 : g0);
-      if ((upper ? m1 : m0) < count) {
+      if ((mine >> m0) & 1u) {
         if (L.outp[0] && acc0[r] != 0.0f) u_atomic_add(L.outp[0], gid * L.outD[0], acc0[r], FIX);
         if (two && L.outp[1] && acc1[r] != 0.0f) u_atomic_add(L.outp[1], gid * L.outD[1], acc1[r], FIX);
       }
@@ -550,13 +555,13 @@ __device__ __forceinline__ void batch_scatter_t(const GroupLanes& L, bool two, i
 // fixed (a deterministic accumulator) is wave-uniform: one branch per
 // flush, each side a straight run of atomics
 template <lv_dtype DT>
-__device__ __forceinline__ void batch_scatter(const GroupLanes& L, bool two, int count,
+__device__ __forceinline__ void batch_scatter(const GroupLanes& L, bool two, uint32_t live,
                                               uint32_t ring_gid, int lane, f32x16 acc0,
                                               f32x16 acc1, bool fixed) {
   if (fixed)
-    batch_scatter_t<DT, true>(L, two, count, ring_gid, lane, acc0, acc1);
+    batch_scatter_t<DT, true>(L, two, live, ring_gid, lane, acc0, acc1);
   else
-    batch_scatter_t<DT, false>(L, two, count, ring_gid, lane, acc0, acc1);
+    batch_scatter_t<DT, false>(L, two, live, ring_gid, lane, acc0, acc1);
 }
 
 // One channel group (at most 64 + 4 channels), one workgroup per (view,
@@ -656,11 +661,11 @@ __global__ __launch_bounds__(kTwo ? 128 : 64, (wide_waves<DT>())) void blend_wid
     {
       const ChanGroup& grp = groups[q.cg];
       const bool takes = group_lanes<DT>(grp, sets, q, lane, L1);
-      two1 = grp.width > 32;
+      two1 = kTwo && grp.width > 32;  // one wave: groups of up to 32 channels only
       if (takes) {
 #pragma unroll
-        for (int b = 0; b < 2; b++)
-  #pragma unroll
+        for (int b = 0; b < (kTwo ? 2 : 1); b++)
+#pragma unroll
           for (int t = 0; t < 4; t++)
             load_row8<DT, PX>(L1, b, q.qy + 2 * t + (lane >> 5), q.qx, q.g, fh[b][t], fl[b][t]);
       }
@@ -675,63 +680,66 @@ __global__ __launch_bounds__(kTwo ? 128 : 64, (wide_waves<DT>())) void blend_wid
   // the rows of a queue, its first hit hit0, into the accumulators
   auto flush = [&](const float* Wt, int count, uint64_t pix, uint32_t hit0) {
     const uint32_t ring_gid = Ids[(hit0 + (uint32_t)(lane & 31)) % kIds];
-    uint32_t ring_cnt = 0u;
-    const uint32_t rows = row_bits(pix);
-    const float* wrow = Wt + (lane & 31) * kWtPitch + 8 * (lane >> 5);
-    if (has_main) {
-      f32x16 acc0 = {}, acc1 = {};
-      batch_mfma<kSplitF>(two1, rows, wrow, fh, fl, acc0, acc1);
-      batch_scatter<DT>(L1, two1, count, ring_gid, lane, acc0, acc1, fixedU);
+    // the rows' sums.  lane l: row l % 32, pixels [32 (l / 32), 32 (l / 32) + 32)
+    const float* rp = Wt + (lane & 31) * kWtPitch + 32 * (lane >> 5);
+    const float* fp = Ft + 32 * (lane >> 5);
+    float bs = 0.0f, ts[kMaxTail] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+      const float4 a = *reinterpret_cast<const float4*>(rp + 4 * k);
+      bs += a.x;
+      bs += a.y;
+      bs += a.z;
+      bs += a.w;
+#pragma unroll
+      for (int t = 0; t < kMaxTail; t++) {
+        if (t < ntail) {  // wave-uniform
+          const float4 f = *reinterpret_cast<const float4*>(fp + t * 64 + 4 * k);
+          ts[t] = __builtin_fmaf(a.x, f.x, ts[t]);
+          ts[t] = __builtin_fmaf(a.y, f.y, ts[t]);
+          ts[t] = __builtin_fmaf(a.z, f.z, ts[t]);
+          ts[t] = __builtin_fmaf(a.w, f.w, ts[t]);
+        }
+      }
     }
-    if (bsets || any_tail || counting) {
-      // lane l: row l % 32, pixels [32 (l / 32), 32 (l / 32) + 32)
-      const float* rp = Wt + (lane & 31) * kWtPitch + 32 * (lane >> 5);
-      const float* fp = Ft + 32 * (lane >> 5);
-      float bs = 0.0f, ts[kMaxTail] = {0.0f, 0.0f, 0.0f, 0.0f};
+    bs += __shfl_xor(bs, 32, 64);
+#pragma unroll
+    for (int t = 0; t < kMaxTail; t++) ts[t] += __shfl_xor(ts[t], 32, 64);
+    uint32_t ring_cnt = 0u;
+    if (counting) {
 #pragma unroll
       for (int k = 0; k < 8; k++) {
         const float4 a = *reinterpret_cast<const float4*>(rp + 4 * k);
-        bs += a.x;
-        bs += a.y;
-        bs += a.z;
-        bs += a.w;
-#pragma unroll
-        for (int t = 0; t < kMaxTail; t++) {
-          if (t < ntail) {  // wave-uniform
-            const float4 f = *reinterpret_cast<const float4*>(fp + t * 64 + 4 * k);
-            ts[t] = __builtin_fmaf(a.x, f.x, ts[t]);
-            ts[t] = __builtin_fmaf(a.y, f.y, ts[t]);
-            ts[t] = __builtin_fmaf(a.z, f.z, ts[t]);
-            ts[t] = __builtin_fmaf(a.w, f.w, ts[t]);
-          }
-        }
+        ring_cnt += (a.x != 0.0f ? 1u : 0u) + (a.y != 0.0f ? 1u : 0u) + (a.z != 0.0f ? 1u : 0u) +
+                    (a.w != 0.0f ? 1u : 0u);
       }
-      bs += __shfl_xor(bs, 32, 64);
-      if (counting) {
-#pragma unroll
-        for (int k = 0; k < 8; k++) {
-          const float4 a = *reinterpret_cast<const float4*>(rp + 4 * k);
-          ring_cnt += (a.x != 0.0f ? 1u : 0u) + (a.y != 0.0f ? 1u : 0u) + (a.z != 0.0f ? 1u : 0u) +
-                      (a.w != 0.0f ? 1u : 0u);
-        }
-        ring_cnt += (uint32_t)__shfl_xor((int)ring_cnt, 32, 64);
-        if (lane < count) {
-          ncontrib += ring_cnt;
-          nrows += ring_cnt ? 1u : 0u;
-        }
+      ring_cnt += (uint32_t)__shfl_xor((int)ring_cnt, 32, 64);
+      if (lane < count) {
+        ncontrib += ring_cnt;
+        nrows += ring_cnt ? 1u : 0u;
+      }
+    }
+    if (lane < count && bs != 0.0f) {  // lane r < 32: row r, whose id and count it holds
+      for (int b = bsets; b; b &= b - 1) {
+        const SetDesc& sd = sets[__builtin_ctz(b)];
+        beta_atomic_add(sd.beta + ring_gid, bs);
+        if (sd.counts) gatomic_add(sd.counts + ring_gid, ring_cnt);
       }
 #pragma unroll
-      for (int t = 0; t < kMaxTail; t++) ts[t] += __shfl_xor(ts[t], 32, 64);
-      if (lane < count && bs != 0.0f) {  // lane r < 32: row r, whose id and count it holds
-        for (int b = bsets; b; b &= b - 1) {
-          const SetDesc& sd = sets[__builtin_ctz(b)];
-          beta_atomic_add(sd.beta + ring_gid, bs);
-          if (sd.counts) gatomic_add(sd.counts + ring_gid, ring_cnt);
-        }
-#pragma unroll
-        for (int t = 0; t < kMaxTail; t++)
-          if (tout[t] && ts[t] != 0.0f) u_atomic_add(tout[t], (int64_t)ring_gid * tD[t], ts[t], fixedU);
-      }
+      for (int t = 0; t < kMaxTail; t++)
+        if (tout[t] && ts[t] != 0.0f) u_atomic_add(tout[t], (int64_t)ring_gid * tD[t], ts[t], fixedU);
+    }
+    // Rows with a contribution (a weight is at least 1e-4 / 255, so their sum is
+    // not 0).  The others are zeros and are not added: their products are zero
+    // only where the features are finite, and a Gaussian that no pixel counts
+    // takes nothing from the view, whatever the map holds there.
+    const uint32_t live = (uint32_t)__ballot(bs != 0.0f) & first_rows(count);
+    if (has_main) {
+      const uint32_t rows = row_bits(pix);
+      const float* wrow = Wt + (lane & 31) * kWtPitch + 8 * (lane >> 5);
+      f32x16 acc0 = {}, acc1 = {};
+      batch_mfma<kSplitF>(two1, rows, wrow, fh, fl, acc0, acc1);
+      batch_scatter<DT>(L1, two1, live, ring_gid, lane, acc0, acc1, fixedU);
     }
   };
   // statistics go to every set whose statistics this work item takes
@@ -799,8 +807,8 @@ __global__ __launch_bounds__(kTwo ? 128 : 64, (wide_waves<DT>())) void blend_wid
     lds_order();  // records in LDS
     // the hit Gaussians in order (a scalar loop over the set bits; each
     // record read from LDS, a broadcast, one hit ahead): each takes the next
-    // row, also where it has no contribution (its row is then zeros, which
-    // add nothing: nearly every hit has one, and a test would cost each hit
+    // row, also where it has no contribution (its row is then zeros and is left
+    // out at the flush: nearly every hit has one, and a test would cost each hit
     // more than the few rows); a full queue is handed over
     int j = (int)__builtin_ctzll(h);
     float4 ra = Rs[j][0];
@@ -1034,7 +1042,7 @@ __global__ __launch_bounds__(64, 2) void blend_pair_kernel(
             }
           }
         }
-        if (pend) batch_scatter<DT>(Lp, twop, count, ring_gid, lane, acc0, acc1, fixedU);
+        if (pend) batch_scatter<DT>(Lp, twop, first_rows(count), ring_gid, lane, acc0, acc1, fixedU);
         pend = false;
         if (!ok) continue;
         acc0 = f32x16{};
@@ -1066,7 +1074,7 @@ __global__ __launch_bounds__(64, 2) void blend_pair_kernel(
         twop = two;
         pend = true;
       }
-      if (pend) batch_scatter<DT>(Lp, twop, count, ring_gid, lane, acc0, acc1, fixedU);
+      if (pend) batch_scatter<DT>(Lp, twop, first_rows(count), ring_gid, lane, acc0, acc1, fixedU);
     } else {
       for (int cg = 0; cg < ngroups; cg++) {
         if (!((gmask >> cg) & 1u)) continue;
@@ -1107,7 +1115,7 @@ __global__ __launch_bounds__(64, 2) void blend_pair_kernel(
             }
           }
         }
-        batch_scatter<DT>(L, two, count, ring_gid, lane, acc0, acc1, fixedU);
+        batch_scatter<DT>(L, two, first_rows(count), ring_gid, lane, acc0, acc1, fixedU);
       }
     }
     __syncthreads();  // rows read before they are written again
