@@ -629,7 +629,18 @@ void scene_cache_clear() {
   g_scene_cache.clear();
 }
 
-// After the device has finished with the buffer (the caller synchronised).
+// Waits for all work of device dev, whichever device is current (a handle may
+// be destroyed by a thread that works on another one).
+void synchronize_device(int dev) {
+  int cur = dev;
+  (void)hipGetDevice(&cur);
+  if (cur != dev) (void)hipSetDevice(dev);
+  (void)hipDeviceSynchronize();
+  if (cur != dev) (void)hipSetDevice(cur);
+}
+
+// After the buffer's device has finished with it (synchronize_device): the next
+// owner may use it on any stream.
 void scene_buf_release(int dev, Buf& b) {
   if (!b.p) return;
   if (b.cap > kSceneCacheMaxBuf) {
@@ -737,11 +748,7 @@ lv_status lv_scene_create(const float* means, const float* scales, const float* 
 
 lv_status lv_scene_destroy(lv_scene* sc) {
   if (!sc) return LV_OK;
-  int cur = sc->device;
-  (void)hipGetDevice(&cur);
-  if (cur != sc->device) (void)hipSetDevice(sc->device);
-  (void)hipDeviceSynchronize();
-  if (cur != sc->device) (void)hipSetDevice(cur);
+  synchronize_device(sc->device);
   scene_buf_release(sc->device, sc->p0);
   scene_buf_release(sc->device, sc->p1);
   scene_buf_release(sc->device, sc->p2);
@@ -1395,7 +1402,7 @@ lv_status lv_graph_csr(const lv_graph* g, int64_t* n, int64_t* nnz, int32_t* row
 
 lv_status lv_graph_destroy(lv_graph* g) {
   if (!g) return LV_OK;
-  (void)hipDeviceSynchronize();
+  synchronize_device(g->device);
   Buf* bufs[] = {&g->row_ptr, &g->col, &g->val, &g->b0, &g->b1, &g->norms, &g->perm,
                  &g->inv, &g->rp2, &g->col2, &g->val2, &g->bin, &g->bout};
   for (Buf* b : bufs) scene_buf_release(g->device, *b);
