@@ -1425,6 +1425,16 @@ lv_status lv_diffuse(const lv_scene* sc, const lv_graph* gc, const void* g0, lv_
   std::lock_guard<std::mutex> lk(g->mu);
   if (g->last) HIP_TRY(hipStreamWaitEvent(s, g->last, 0));
   else HIP_TRY(hipEventCreateWithFlags(&g->last, hipEventDisableTiming));
+  // from here on every return records the event: what a failed call has queued
+  // (the order's arrays, the shared buffers) is waited for by the next one too
+  struct Record {
+    hipEvent_t e;
+    hipStream_t s;
+    bool done = false;
+    ~Record() {
+      if (!done) (void)hipEventRecord(e, s);
+    }
+  } record{g->last, s};
   const bool order = sc && g->n > 0 && steps > 0;
   const size_t sig = dtype_size(dtype) * (size_t)(g->n > 0 ? g->n : 1) * D;
   const auto grow = [&](Buf& b, size_t bytes) {  // a first buffer from the cache
@@ -1467,6 +1477,7 @@ lv_status lv_diffuse(const lv_scene* sc, const lv_graph* gc, const void* g0, lv_
                            g0, dtype, D, steps, out, g->b0.as<float>(), g->b1.as<float>(),
                            g->norms.as<float>(), s));
   }
+  record.done = true;
   HIP_TRY(hipEventRecord(g->last, s));
   return LV_OK;
 }

@@ -242,11 +242,47 @@ void destroy_on_other_device() {
   CHECK(g_device == 0);
 }
 
+// Calls on one graph share its buffers, also where a call fails half-way: what it
+// has queued is ordered before the next call on another stream.
+void order_after_failed_diffusion() {
+  for (int launch = 0; launch < 2; launch++) {
+    lv_scene* sc = make_scene(100, S1);
+    lv_graph* g = make_graph(100, 3, S1);
+    float* x = static_cast<float*>(device_mem(4 * 100 * 16));
+    if (launch) {
+      fail_after = "spmm";
+    } else {  // the third buffer of the signal's size: after the graph's order is queued
+      fail_size = 4 * 800 + 4 * 800 / 8 + 256;
+      fail_skip = 2;
+    }
+    CHECK(lv_diffuse(sc, g, x, LV_F32, 8, 2, x + 800, S1) == (launch ? LV_ERR_DEVICE : LV_ERR_OUT_OF_MEMORY));
+    fail_size = 0;
+    fail_after.clear();
+    void* event = nullptr;
+    int queued = 0;
+    for (const Op& o : ops()) {
+      if (o.kind == kLaunch && o.stream == S1) queued++, event = nullptr;
+      if (o.kind == kRecord && o.stream == S1) event = o.p;
+    }
+    CHECK(queued > 0);
+    CHECK(event);
+    const size_t at = ops().size();
+    CHECK(lv_diffuse(sc, g, x, LV_F32, 4, 2, x + 800, S2) == LV_OK);
+    bool waits = false;
+    for (size_t i = at; i < ops().size() && ops()[i].kind != kLaunch; i++)
+      waits = waits || (ops()[i].kind == kWait && ops()[i].stream == S2 && ops()[i].p == event);
+    CHECK(waits);
+    ops().clear();
+    CHECK(lv_graph_destroy(g) == LV_OK && lv_scene_destroy(sc) == LV_OK && lv_release_scratch(nullptr, 1) == LV_OK);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> tests = {
       {"destroy_on_other_device", destroy_on_other_device},
+      {"order_after_failed_diffusion", order_after_failed_diffusion},
   };
   CHECK(argc == 2 && tests.count(argv[1]));
   tests.at(argv[1])();
