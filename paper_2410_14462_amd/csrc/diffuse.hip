@@ -148,13 +148,14 @@ __global__ __launch_bounds__(256) void spmm_kernel(const int32_t* __restrict__ r
       const int64_t row = (tile * 4 + (t >> 6)) * R + sub;
       const bool valid = row < n;
       const bool live = valid && ch < D;
-      const int32_t a = valid ? row_ptr[row] : 0, b = valid ? row_ptr[row + 1] : 0;
+      // edges in 32 unsigned bits: a step past the last of 2^31 - 1 does not wrap
+      const uint32_t a = valid ? row_ptr[row] : 0, b = valid ? row_ptr[row + 1] : 0;
       float acc = 0.0f;
-      for (int32_t e0 = a; e0 < b; e0 += C) {
-        const int32_t my = e0 + c;
+      for (uint32_t e0 = a; e0 < b; e0 += C) {
+        const uint32_t my = e0 + c;
         const int32_t cv = my < b ? col[my] : 0;
         const float wv = my < b ? ld<VT>(val, my) : 0.0f;
-        const int cnt = b - e0 < C ? b - e0 : C;
+        const int cnt = b - e0 < C ? (int)(b - e0) : C;
         for (int j = 0; j < cnt; j += U) {
           // U gathers in flight; slots past the row's end read column 0 of a
           // valid row with weight 0 (lanes past the end hold col 0, w 0)
@@ -239,15 +240,16 @@ __global__ __launch_bounds__(256) void spmm_rows_kernel(const int32_t* __restric
   for (int64_t tile = t0 + (blockIdx.x >> 3); tile < t1; tile += nloc) {
     const int64_t row0 = tile * 256 + 64 * wv, row = row0 + lane;
     if (row0 >= n) continue;  // wave-uniform
-    const int32_t a = row_ptr[row < n ? row : n], b = row_ptr[row < n ? row + 1 : n];
-    const int32_t first = __shfl(a, 0, 64), last = __shfl(b, 63, 64);
+    // edges in 32 unsigned bits: a round past the last of 2^31 - 1 does not wrap
+    const uint32_t a = row_ptr[row < n ? row : n], b = row_ptr[row < n ? row + 1 : n];
+    const uint32_t first = __shfl(a, 0, 64), last = __shfl(b, 63, 64);
     float acc[ND] = {};
-    for (int32_t base = first; base < last; base += E) {
+    for (uint32_t base = first; base < last; base += E) {
       int32_t cj[U];
       float w[U], x[U][ND];
 #pragma unroll
       for (int u = 0; u < U; u++) {
-        const int32_t e = base + 64 * u + lane;
+        const uint32_t e = base + 64 * u + lane;
         const bool ok = e < last;
         cj[u] = ok ? col[e] : 0;
         w[u] = ok ? ld<VT>(val, e) : 0.0f;
@@ -266,9 +268,9 @@ __global__ __launch_bounds__(256) void spmm_rows_kernel(const int32_t* __restric
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
-      const int32_t e0 = (a > base ? a : base) - base;
-      const int32_t e1 = (b < base + E ? b : base + E) - base;
-      for (int32_t e = e0; e < e1; e++) {
+      const int e0 = (int)((a > base ? a : base) - base);
+      const int e1 = (int)(b < base + E ? b - base : E);  // negative where the row ends before the round
+      for (int e = e0; e < e1; e++) {
         const float we = st_[ND][e];
 #pragma unroll
         for (int k = 0; k < ND; k++) acc[k] = __builtin_fmaf(we, st_[k][e], acc[k]);
@@ -717,10 +719,10 @@ __global__ __launch_bounds__(256) void permute_csr_kernel(
     return;
   }
   const int64_t o = perm[r];
-  const int32_t a = rp[o], b = rp[o + 1];
+  const uint32_t a = rp[o], b = rp[o + 1];  // unsigned: a step past 2^31 - 1 does not wrap
   const int64_t d = off[r];
   if (sub == 0) rp2[r] = (int32_t)d;
-  for (int32_t e = a + sub; e < b; e += 16) {
+  for (uint32_t e = a + sub; e < b; e += 16) {
     col2[d + (e - a)] = (int32_t)inv[col[e]];
     val2[d + (e - a)] = val[e];
   }
