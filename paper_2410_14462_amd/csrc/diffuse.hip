@@ -45,14 +45,24 @@ inline int norm_slots(int D) {
 
 // Sum over the slots of channel ch, the same in every block (a fixed order);
 // threads t, t + C, ... of the block's 256 hold the same channel, C a power of
-// two up to 64.  red: 4 C floats of LDS.
-template <int C>
+// two up to 64.  A thread loads T of its 64 C / 256 slots at a time: one after
+// the other they were most of a small step (500 rows, D = 64 in FP32: 10.4 us,
+// 7.4 with all 16 together).  red: 4 C floats of LDS.
+template <int C, int T>
 __device__ __forceinline__ float slot_sum(const float* __restrict__ nrm, int slots, int D, int ch,
                                           float* red) {
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   float v = 0.0f;
-  if (ch < D)
-    for (int k = t / C; k < slots; k += 256 / C) v += nrm[(int64_t)k * D + ch];
+  for (int k0 = t / C; k0 < slots; k0 += T * (256 / C)) {
+    float x[T];
+#pragma unroll
+    for (int u = 0; u < T; u++) {
+      const int k = k0 + u * (256 / C);
+      x[u] = ch < D && k < slots ? nrm[(int64_t)k * D + ch] : 0.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < T; u++) v += x[u];
+  }
 #pragma unroll
   for (int off = C; off < 64; off <<= 1) v += __shfl_xor(v, off, 64);
   if (lane < C) red[w * C + lane] = v;
@@ -136,7 +146,7 @@ __global__ __launch_bounds__(256) void spmm_kernel(const int32_t* __restrict__ r
   for (int k = 0; k < cpl; k += 1) {
     const int ch = c + k * C;
     const int64_t chc = ch < D ? ch : 0;
-    const float n2 = slot_sum<C>(nrm_in, slots, D, ch, sq);
+    const float n2 = slot_sum<C, (C < 16 ? 2 : 4)>(nrm_in, slots, D, ch, sq);
     const float scl = n2 > 0.0f ? 1.0f / sqrtf(n2) : 0.0f;
     float ss = 0.0f;  // this lane's sum of squares of channel ch
     // Workgroups go to the 8 XCDs round-robin: XCD x (= blockIdx mod 8)
@@ -205,7 +215,7 @@ __device__ __forceinline__ float stored(float x) {
   }
 }
 
-// Few channels (D = ND, at most 4): one row per lane, 64 consecutive rows per
+// Few channels (D = ND, at most 4): one row per lane, RW consecutive rows per
 // wave, whose edges are one contiguous range.  The wave takes that range 64 U
 // edges at a time, one edge per lane and load: columns and weights are read
 // coalesced, U gathers are in flight per lane, and the weights and gathered
@@ -214,7 +224,10 @@ __device__ __forceinline__ float stored(float x) {
 // row in global memory instead (8 edges at a time) every load touched one line
 // per lane.  A D = 1 FP32 step on a million rows: 50 -> 27 us with 13.6 edges a
 // row (121 MB: the rate of a large copy, 4.5 TB/s), 132 -> 41 us with 22.6.
-template <int ND, lv_dtype GT, lv_dtype VT>
+// RW = 64 (a round of edges per 28 rows of 18) where there are rows enough; a
+// small graph's step lasts as long as one wave's chain of rounds, and 16 rows
+// are one round (see spmm_rows_launch).
+template <int ND, int RW, lv_dtype GT, lv_dtype VT>
 __global__ __launch_bounds__(256) void spmm_rows_kernel(const int32_t* __restrict__ row_ptr,
                                                         const int32_t* __restrict__ col,
                                                         const void* __restrict__ val, int64_t n,
@@ -228,21 +241,23 @@ __global__ __launch_bounds__(256) void spmm_rows_kernel(const int32_t* __restric
   float scl[ND], ss[ND];
 #pragma unroll
   for (int k = 0; k < ND; k++) {
-    const float n2 = slot_sum<1>(nrm_in, slots, ND, k, sq);
+    const float n2 = slot_sum<1, 1>(nrm_in, slots, ND, k, sq);
     scl[k] = n2 > 0.0f ? 1.0f / sqrtf(n2) : 0.0f;
     ss[k] = 0.0f;
   }
   float(*st_)[E] = stage[wv];
   // XCD x (= blockIdx mod 8) takes the x-th eighth of the rows (locality order)
-  const int64_t tiles = (n + 255) / 256;
+  const int64_t tiles = (n + 4 * RW - 1) / (4 * RW);
   const int64_t xcd = blockIdx.x & 7, nloc = gridDim.x >> 3;
   const int64_t t0 = tiles * xcd / 8, t1 = tiles * (xcd + 1) / 8;
   for (int64_t tile = t0 + (blockIdx.x >> 3); tile < t1; tile += nloc) {
-    const int64_t row0 = tile * 256 + 64 * wv, row = row0 + lane;
+    const int64_t row0 = (tile * 4 + wv) * RW, row = row0 + (lane < RW ? lane : RW);
     if (row0 >= n) continue;  // wave-uniform
-    // edges in 32 unsigned bits: a round past the last of 2^31 - 1 does not wrap
-    const uint32_t a = row_ptr[row < n ? row : n], b = row_ptr[row < n ? row + 1 : n];
-    const uint32_t first = __shfl(a, 0, 64), last = __shfl(b, 63, 64);
+    // edges in 32 unsigned bits: a round past the last of 2^31 - 1 does not wrap;
+    // lanes past the wave's rows have none
+    const uint32_t a = row_ptr[row < n ? row : n], b = row_ptr[row < n ? (lane < RW ? row + 1 : row) : n];
+    const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)a, 0);
+    const uint32_t last = (uint32_t)__builtin_amdgcn_readlane((int)b, RW - 1);
     float acc[ND] = {};
     for (uint32_t base = first; base < last; base += E) {
       int32_t cj[U];
@@ -276,7 +291,7 @@ __global__ __launch_bounds__(256) void spmm_rows_kernel(const int32_t* __restric
         for (int k = 0; k < ND; k++) acc[k] = __builtin_fmaf(we, st_[k][e], acc[k]);
       }
     }
-    if (row < n) {
+    if (lane < RW && row < n) {
 #pragma unroll
       for (int k = 0; k < ND; k++) {
         const float o = stored<GT>(scl[k] * acc[k]);  // the norm of what is stored
@@ -298,10 +313,10 @@ __global__ __launch_bounds__(256) void spmm_rows_kernel(const int32_t* __restric
   }
 }
 
-// D = 8, 16, 32 or 64 channels in rows of 16-byte pieces: C channels per lane (4
-// in FP32, 8 in BF16: one 16-byte load), L = D / C lanes per row, R = 64 / L
-// consecutive rows per wave, whose edges are one contiguous range.  The wave
-// takes that range E edges at a time: columns and weights are read coalesced and
+// D = 8, 16, 32 or 64 channels in rows of pieces of C channels, one load each (4
+// channels in FP32, 8 in BF16: 16 bytes; 4 in small graphs), one piece per lane,
+// L = D / C lanes per row, R = 64 / L consecutive rows per wave, whose edges are
+// one contiguous range.  The wave takes that range E edges at a time: columns and weights are read coalesced and
 // left in LDS as (row offset, weight); each row's lanes then walk the row's part,
 // U gathers in flight, and sum in edge order with the same fused multiply-adds as
 // spmm_kernel.
@@ -314,18 +329,22 @@ __global__ __launch_bounds__(256) void spmm_rows_kernel(const int32_t* __restric
 // 8 and 12 gathers in flight 4 is the fastest or level everywhere (D = 64 in
 // FP32, 1M rows: 252, 269, 272, 303 us a step).  Steps, 16 edges a row, before and
 // now: 1M rows, D = 64, BF16 207 -> 144 us (338 MB: 2.3 TB/s), FP32 260 -> 252;
-// 300k rows, D = 32, BF16 50 -> 29, D = 16 30 -> 21, D = 8 28 -> 17; 5,000 rows,
-// D = 16 11.2 -> 9.8, D = 64 11.3 -> 12.1 (half as many waves there).
+// 300k rows, D = 32, BF16 50 -> 29, D = 16 30 -> 21, D = 8 28 -> 17.  In a graph
+// so small that no block takes a second tile (see spmm_wide_launch) a step lasts
+// as long as one wave's chain: there U = 8, and four channels per lane also in
+// BF16, twice as many waves.
 // kBig: offsets of g do not fit 32 bits (else they are formed when staged, and a
 // gather is one addition and one load).
-template <int D, lv_dtype GT, lv_dtype VT, bool kBig>
+template <int D, int C, int U, lv_dtype GT, lv_dtype VT, bool kBig>
 __global__ __launch_bounds__(256) void spmm_wide_kernel(const int32_t* __restrict__ row_ptr,
                                                         const int32_t* __restrict__ col,
                                                         const void* __restrict__ val, int64_t n,
                                                         const void* __restrict__ g,
                                                         const float* __restrict__ nrm_in, int slots,
                                                         void* __restrict__ y, float* __restrict__ nrm_out) {
-  constexpr int C = GT == LV_F32 ? 4 : 8, L = D / C, R = 64 / L, U = 4;
+  constexpr int L = D / C, R = 64 / L;
+  constexpr int kPiece = C * (GT == LV_F32 ? 4 : 2), kWords = kPiece / 4;  // bytes and words of a lane's piece of a row
+  typedef uint32_t piece_t __attribute__((ext_vector_type(kWords)));
   constexpr int E = R > 32 ? 16 * R : 512, P = R < 32 ? 4 : 8;  // edges per round, per lane and load
   constexpr uint32_t kRowBytes = D * (GT == LV_F32 ? 4 : 2);
   __shared__ union {
@@ -340,14 +359,13 @@ __global__ __launch_bounds__(256) void spmm_wide_kernel(const int32_t* __restric
   // a gathered row's piece of this lane
   const auto gather = [&](uint32_t off) {
     if constexpr (kBig)
-      return *reinterpret_cast<const uint4*>(gb + (uint64_t)off * kRowBytes + 16 * cl);
+      return *reinterpret_cast<const piece_t*>(gb + (uint64_t)off * kRowBytes + kPiece * cl);
     else
-      return *reinterpret_cast<const uint4*>(gb + (off + 16u * (uint32_t)cl));
+      return *reinterpret_cast<const piece_t*>(gb + (off + (uint32_t)(kPiece * cl)));
   };
-  const auto add = [&](float (&acc)[C], float w, const uint4& q) {
-    const uint32_t r[4] = {q.x, q.y, q.z, q.w};
+  const auto add = [&](float (&acc)[C], float w, const piece_t& r) {
 #pragma unroll
-    for (int k = 0; k < 4; k++) {
+    for (int k = 0; k < kWords; k++) {
       if constexpr (GT == LV_F32) {
         acc[k] = __builtin_fmaf(w, __uint_as_float(r[k]), acc[k]);
       } else {
@@ -384,7 +402,7 @@ __global__ __launch_bounds__(256) void spmm_wide_kernel(const int32_t* __restric
   int32_t first = __builtin_amdgcn_readlane(a, 0), last = __builtin_amdgcn_readlane(b, 63);
   if (first < last) load_edges(first, last - first);
   {
-    const float n2 = slot_sum<D>(nrm_in, slots, D, t & (D - 1), sh.sq);
+    const float n2 = slot_sum<D, D / 4>(nrm_in, slots, D, t & (D - 1), sh.sq);
     if (t < D) scales[t] = n2 > 0.0f ? 1.0f / sqrtf(n2) : 0.0f;
     __syncthreads();
   }
@@ -413,7 +431,7 @@ __global__ __launch_bounds__(256) void spmm_wide_kernel(const int32_t* __restric
       const int32_t j1 = b - base < m ? b - base : m;
       for (; j + U <= j1; j += U) {
         uint2 ed[U];
-        uint4 x[U];
+        piece_t x[U];
 #pragma unroll
         for (int u = 0; u < U; u++) {
           ed[u] = edge[j + u];
@@ -424,7 +442,7 @@ __global__ __launch_bounds__(256) void spmm_wide_kernel(const int32_t* __restric
       }
       if (j < j1) {  // fewer than U left: the last edge's row again, taken as zeros
         uint2 ed[U];
-        uint4 x[U];
+        piece_t x[U];
 #pragma unroll
         for (int u = 0; u < U; u++) {
           ed[u] = edge[j + u < j1 ? j + u : j1 - 1];
@@ -433,7 +451,9 @@ __global__ __launch_bounds__(256) void spmm_wide_kernel(const int32_t* __restric
 #pragma unroll
         for (int u = 0; u < U; u++) {
           const bool ok = j + u < j1;
-          const uint4 z = make_uint4(ok ? x[u].x : 0u, ok ? x[u].y : 0u, ok ? x[u].z : 0u, ok ? x[u].w : 0u);
+          piece_t z;
+#pragma unroll
+          for (int k = 0; k < kWords; k++) z[k] = ok ? x[u][k] : 0u;
           add(acc, ok ? __uint_as_float(ed[u].y) : 0.0f, z);
         }
       }
@@ -451,14 +471,15 @@ __global__ __launch_bounds__(256) void spmm_wide_kernel(const int32_t* __restric
         o[k] = stored<GT>(scales[C * cl + k] * acc[k]);  // the norm of what is stored
         ss[k] = __builtin_fmaf(o[k], o[k], ss[k]);
       }
-      uint4 q;
-      if constexpr (GT == LV_F32) {
-        q = make_uint4(__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3]));
-      } else {
-        const auto pack = [&](int k) { return (__float_as_uint(o[k]) >> 16) | __float_as_uint(o[k + 1]); };
-        q = make_uint4(pack(0), pack(2), pack(4), pack(6));
+      piece_t q;
+#pragma unroll
+      for (int k = 0; k < kWords; k++) {
+        if constexpr (GT == LV_F32)
+          q[k] = __float_as_uint(o[k]);
+        else
+          q[k] = (__float_as_uint(o[2 * k]) >> 16) | __float_as_uint(o[2 * k + 1]);
       }
-      *reinterpret_cast<uint4*>(static_cast<char*>(y) + row * (int64_t)kRowBytes + 16 * cl) = q;
+      *reinterpret_cast<piece_t*>(static_cast<char*>(y) + row * (int64_t)kRowBytes + kPiece * cl) = q;
     }
   }
   // per-channel sums over the block: threads t = cl (mod L) hold channels C cl ..
@@ -510,29 +531,48 @@ hipError_t spmm_launch(const int32_t* rp, const int32_t* col, const void* val, i
 // row, BF16) and 262, 252, 260 and 293 in FP32.
 constexpr int64_t kSpmmWideBlocks = 1280;
 
+// Up to this many tiles the small form of spmm_wide_kernel runs (C = 4, U = 8).
+// Steps of 18 edges a row, small / large form: D = 64, 5,000 rows (313 tiles) FP32
+// 7.2 / 7.6 us, BF16 7.2 / 8.8; 15,000 rows (938) 9.3 / 9.0 and 9.1 / 9.5; 50,000
+// rows (3125) 17.4 / 16.9 and 17.2 / 14.0; D = 8, 50,000 rows (391) 9.2 / 9.3 and
+// 9.2 / 10.3; 300,000 rows (2344) 28.8 / 26.0 and 26.0 / 25.3.
+constexpr int64_t kFewTiles = 1024;
+
 template <int D, lv_dtype GT, lv_dtype VT>
 hipError_t spmm_wide_launch(const int32_t* rp, const int32_t* col, const void* val, int64_t n,
                             const void* g, const float* nin, int slots, void* y, float* nout,
                             hipStream_t s) {
-  constexpr int R = 64 * (GT == LV_F32 ? 4 : 8) / D;  // rows per wave
-  const int64_t tiles = (n + 4 * R - 1) / (4 * R);
+  constexpr int C = GT == LV_F32 ? 4 : 8;  // channels of a 16-byte piece
+  const bool few = n * D <= kFewTiles * 1024;
+  const int rows = 256 * (few ? 4 : C) / D;  // per tile
+  const int64_t tiles = (n + rows - 1) / rows;
   const int64_t want = (tiles + 7) / 8 * 8;
   const unsigned blocks = (unsigned)(want < kSpmmWideBlocks ? want : kSpmmWideBlocks);
   const bool big = n * D * (GT == LV_F32 ? 4 : 2) > (int64_t)1 << 32;
-  hipLaunchKernelGGL((big ? spmm_wide_kernel<D, GT, VT, true> : spmm_wide_kernel<D, GT, VT, false>),
+  hipLaunchKernelGGL((few   ? spmm_wide_kernel<D, 4, 8, GT, VT, false>
+                      : big ? spmm_wide_kernel<D, C, 4, GT, VT, true>
+                            : spmm_wide_kernel<D, C, 4, GT, VT, false>),
                      dim3(blocks), dim3(256), 0, s, rp, col, val, n, g, nin, slots, y, nout);
   return hipGetLastError();
 }
 
+// The fewest rows per wave, 16, 32 or 64, that need at most 2048 waves (two per
+// SIMD), else 64.  D = 1 in FP32, 18 edges a row, a step of 16 / 32 / 64 rows per
+// wave: 5,000 rows 6.9 / 8.7 / 10.9 us, 15,000 7.6 / 8.7 / 11.0, 50,000 11.1 / 10.3
+// / 11.3, 120,000 18.4 / 13.9 / 13.1; D = 4, 15,000 8.7 / 11.2 / 13.7, 50,000 15.6 /
+// 12.0 / 13.7, 120,000 23.2 / 21.2 / 15.5.
 template <int ND, lv_dtype GT, lv_dtype VT>
 hipError_t spmm_rows_launch(const int32_t* rp, const int32_t* col, const void* val, int64_t n,
                             const void* g, const float* nin, int slots, void* y, float* nout,
                             hipStream_t s) {
-  const int64_t tiles = (n + 255) / 256;
+  const int rows = n <= 16 * 2048 ? 16 : n <= 32 * 2048 ? 32 : 64;
+  const int64_t tiles = (n + 4 * rows - 1) / (4 * rows);
   const int64_t want = (tiles + 7) / 8 * 8;
   const unsigned blocks = (unsigned)(want < 8192 ? want : 8192);
-  hipLaunchKernelGGL((spmm_rows_kernel<ND, GT, VT>), dim3(blocks), dim3(256), 0, s, rp, col, val, n, g, nin,
-                     slots, y, nout);
+  hipLaunchKernelGGL((rows == 16   ? spmm_rows_kernel<ND, 16, GT, VT>
+                      : rows == 32 ? spmm_rows_kernel<ND, 32, GT, VT>
+                                   : spmm_rows_kernel<ND, 64, GT, VT>),
+                     dim3(blocks), dim3(256), 0, s, rp, col, val, n, g, nin, slots, y, nout);
   return hipGetLastError();
 }
 
