@@ -225,16 +225,18 @@ __global__ __launch_bounds__(256) void encode_fp8_quad_kernel(const float4* __re
   }
 }
 
-// Pixel-block layout for D a multiple of 4, aligned: a thread takes four
-// channels of a block of 8 pixels (eight 16-byte loads, consecutive threads on
-// consecutive channels), the last blocks first.  1008x756x384 in FP8: 347 us
-// one channel per thread with the IEEE division and the conversion in software
-// (about 30 vector operations an element), 253 now.
-template <lv_dtype E>
-__global__ __launch_bounds__(256) void encode_px8_quad_kernel(const float4* __restrict__ src, int W, int Q,
-                                                              uint32_t runs4, const uint32_t* __restrict__ amax,
-                                                              float* __restrict__ scales,
-                                                              void* __restrict__ dst) {
+// FP8 pixel blocks for D a multiple of 4, aligned: a thread takes four channels
+// of a block of 8 pixels (eight 16-byte loads, consecutive threads on
+// consecutive channels), the last blocks first.  Bound by its instructions and
+// then its reads: 1008x756x384 347 us one channel per thread with the IEEE
+// division and the conversion in software (about 30 vector operations an
+// element), 253 now.  FP32 and BF16, with next to none, stay on the kernel below,
+// whose lanes store consecutive runs (1008x756x64: 68 us, 97 in this form, BF16
+// 43 and 53).
+__global__ __launch_bounds__(256) void encode_fp8_px8_quad_kernel(const float4* __restrict__ src, int W, int Q,
+                                                                  uint32_t runs4, const uint32_t* __restrict__ amax,
+                                                                  float* __restrict__ scales,
+                                                                  uint2* __restrict__ dst) {
   const uint32_t W8 = (uint32_t)(W + 7) >> 3;
   const uint32_t r = blockIdx.x * 256u + threadIdx.x;
   if (r >= runs4) return;
@@ -245,51 +247,30 @@ __global__ __launch_bounds__(256) void encode_px8_quad_kernel(const float4* __re
 #pragma unroll
   for (int i = 0; i < 8; i++)
     v[i] = x0 + i < W ? src[((int64_t)y * W + x0 + i) * Q + q] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  const int64_t run = 4 * ((int64_t)blk * Q + q);  // the thread's first run of 8 pixels
-  if constexpr (E == LV_FP8_E4M3) {
-    ChanScale cs[4];
+  ChanScale cs[4];
 #pragma unroll
-    for (int c = 0; c < 4; c++) cs[c].set(__uint_as_float(amax[4 * q + c]));
-    const bool plain = cs[0].rc != 0.0f && cs[1].rc != 0.0f && cs[2].rc != 0.0f && cs[3].rc != 0.0f;
-    if (blk == 0)
+  for (int c = 0; c < 4; c++) cs[c].set(__uint_as_float(amax[4 * q + c]));
+  const bool plain = cs[0].rc != 0.0f && cs[1].rc != 0.0f && cs[2].rc != 0.0f && cs[3].rc != 0.0f;
+  if (blk == 0)
 #pragma unroll
-      for (int c = 0; c < 4; c++) scales[4 * q + c] = cs[c].sc;
-    uint4 o[2];
-    uint32_t* const ow = reinterpret_cast<uint32_t*>(o);
+    for (int c = 0; c < 4; c++) scales[4 * q + c] = cs[c].sc;
+  uint4 o[2];
+  uint32_t* const ow = reinterpret_cast<uint32_t*>(o);
 #pragma unroll
-    for (int c = 0; c < 4; c++) {
-      float x[8];
+  for (int c = 0; c < 4; c++) {
+    float x[8];
 #pragma unroll
-      for (int i = 0; i < 8; i++) {
-        const float u = c == 0 ? v[i].x : c == 1 ? v[i].y : c == 2 ? v[i].z : v[i].w;
-        x[i] = plain ? cs[c].div(u) : u / cs[c].sc;
-      }
-      ow[2 * c] = e4m3x2(x[0], x[1]) | (e4m3x2(x[2], x[3]) << 16);
-      ow[2 * c + 1] = e4m3x2(x[4], x[5]) | (e4m3x2(x[6], x[7]) << 16);
+    for (int i = 0; i < 8; i++) {
+      const float u = c == 0 ? v[i].x : c == 1 ? v[i].y : c == 2 ? v[i].z : v[i].w;
+      x[i] = plain ? cs[c].div(u) : u / cs[c].sc;
     }
-    uint4* const d = reinterpret_cast<uint4*>(static_cast<uint2*>(dst) + run);
-    d[0] = o[0];
-    d[1] = o[1];
-  } else {
-#pragma unroll
-    for (int c = 0; c < 4; c++) {
-      float x[8];
-#pragma unroll
-      for (int i = 0; i < 8; i++) x[i] = c == 0 ? v[i].x : c == 1 ? v[i].y : c == 2 ? v[i].z : v[i].w;
-      if constexpr (E == LV_F32) {
-        float4* const d = static_cast<float4*>(dst) + 2 * (run + c);
-        d[0] = make_float4(x[0], x[1], x[2], x[3]);
-        d[1] = make_float4(x[4], x[5], x[6], x[7]);
-      } else {
-        uint4 o;
-        o.x = (uint32_t)to_bf16(x[0]) | ((uint32_t)to_bf16(x[1]) << 16);
-        o.y = (uint32_t)to_bf16(x[2]) | ((uint32_t)to_bf16(x[3]) << 16);
-        o.z = (uint32_t)to_bf16(x[4]) | ((uint32_t)to_bf16(x[5]) << 16);
-        o.w = (uint32_t)to_bf16(x[6]) | ((uint32_t)to_bf16(x[7]) << 16);
-        static_cast<uint4*>(dst)[run + c] = o;
-      }
-    }
+    ow[2 * c] = e4m3x2(x[0], x[1]) | (e4m3x2(x[2], x[3]) << 16);
+    ow[2 * c + 1] = e4m3x2(x[4], x[5]) | (e4m3x2(x[6], x[7]) << 16);
   }
+  // the thread's four runs of 8 codes
+  uint4* const d = reinterpret_cast<uint4*>(dst + 4 * ((int64_t)blk * Q + q));
+  d[0] = o[0];
+  d[1] = o[1];
 }
 
 // Pixel-block layout: thread k writes element (block k / D, channel k % D):
@@ -348,10 +329,10 @@ hipError_t launch_encode(const float* src, int64_t pixels, int D, lv_dtype dtype
     return hipMemcpyAsync(dst, src, (size_t)total * sizeof(float), hipMemcpyDeviceToDevice, s);
   }
   const int64_t runs = px8 ? pixels / W * ((W + 7) / 8) * (int64_t)D : 0;
-  // four channels per thread: D a multiple of 4, 16-byte loads (a pixel-block
-  // run of four channels is then 32 bytes or more in every element type), HWC
-  // codes in 4-byte stores, and thread indices that fit 32 bits
-  const bool quad = D % 4 == 0 && (uintptr_t)src % 16 == 0 &&
+  // FP8 with four channels per thread: D a multiple of 4, 16-byte loads (a
+  // pixel-block run of four channels is then 32 bytes), HWC codes in 4-byte
+  // stores, and thread indices that fit 32 bits
+  const bool quad = el == LV_FP8_E4M3 && D % 4 == 0 && (uintptr_t)src % 16 == 0 &&
                     (px8 ? (uintptr_t)dst % 16 == 0 && runs / 4 < 0xFFFFFF00ll : (uintptr_t)dst % 4 == 0);
   const int Q = D / 4;
   const float4* const src4 = reinterpret_cast<const float4*>(src);
@@ -372,11 +353,8 @@ hipError_t launch_encode(const float* src, int64_t pixels, int D, lv_dtype dtype
     }
   }
   if (px8 && quad) {
-    const unsigned nb = (unsigned)((runs / 4 + 255) / 256);
-    const auto kernel = el == LV_F32    ? encode_px8_quad_kernel<LV_F32>
-                        : el == LV_BF16 ? encode_px8_quad_kernel<LV_BF16>
-                                        : encode_px8_quad_kernel<LV_FP8_E4M3>;
-    hipLaunchKernelGGL(kernel, dim3(nb), dim3(256), 0, s, src4, W, Q, (uint32_t)(runs / 4), amax, scales, dst);
+    hipLaunchKernelGGL(encode_fp8_px8_quad_kernel, dim3((unsigned)((runs / 4 + 255) / 256)), dim3(256), 0, s, src4, W,
+                       Q, (uint32_t)(runs / 4), amax, scales, static_cast<uint2*>(dst));
     return hipGetLastError();
   }
   if (px8) {
@@ -387,7 +365,7 @@ hipError_t launch_encode(const float* src, int64_t pixels, int D, lv_dtype dtype
     hipLaunchKernelGGL(kernel, dim3(nb), dim3(256), 0, s, src, W, D, runs, scales, dst);
     return hipGetLastError();
   }
-  if (el == LV_FP8_E4M3 && quad) {
+  if (quad) {
     const int64_t want = (total / 4 + 255) / 256;
     const unsigned nb = (unsigned)std::max<int64_t>((Q + 255) / 256, std::min<int64_t>(want, 4096));
     hipLaunchKernelGGL(encode_fp8_quad_kernel, dim3(nb), dim3(256), 0, s, src4, total / 4, Q, amax, scales,
