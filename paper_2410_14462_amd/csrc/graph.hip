@@ -416,18 +416,19 @@ __global__ __launch_bounds__(256) void norms_kernel(const float* __restrict__ f,
 // neighbour's row is then read again by its other neighbours while it is in
 // the caches, and 64 / L edges share one pass of the sum, the exponential and
 // the division.  1M nodes, k = 16, D = 64: 4.1 ms with a wave per node, nodes
-// in the caller's order; 0.59 now (the 4.1 GB of gathered rows at 7 TB/s).
+// in the caller's order; 0.59 now (the 4.1 GB of gathered rows at 7 TB/s).  A
+// launch takes the edges [first, end): a grid holds fewer than 2^32 threads.
 template <int L>
-__global__ __launch_bounds__(256) void edge_weights_kernel(const float* __restrict__ f, int64_t n, int D,
-                                                           int k, bool vec, const uint32_t* __restrict__ sid,
+__global__ __launch_bounds__(256) void edge_weights_kernel(const float* __restrict__ f, int64_t first, int64_t end,
+                                                           int D, int k, bool vec, const uint32_t* __restrict__ sid,
                                                            const int32_t* __restrict__ pos,
                                                            const double* __restrict__ d2,
                                                            const double* __restrict__ nrm,
                                                            const double* __restrict__ sig2,
                                                            double* __restrict__ w) {
-  const int64_t e = (xcd_block() * blockDim.x + threadIdx.x) / L;
+  const int64_t e = first + (xcd_block() * blockDim.x + threadIdx.x) / L;
   const int sub = threadIdx.x % L;
-  if (e >= n * k) return;
+  if (e >= end) return;
   const int64_t i = sid[e / k], j = sid[pos[e]];
   const double dot = lane_sum<L>(part_dot<L>(f + i * D, f + j * D, D, sub, vec));
   if (sub == 0) {
@@ -783,8 +784,12 @@ hipError_t build_knn_graph(const float4* centres, int64_t n, const float* feats,
       const auto weights = lanes == 1   ? edge_weights_kernel<1>
                            : lanes == 4 ? edge_weights_kernel<4>
                                         : edge_weights_kernel<16>;
-      hipLaunchKernelGGL(weights, dim3(grid1(nk * lanes)), dim3(256), 0, s, feats, n, D, k, vec, sid, pos, d2,
-                         nrm, sig2, w);
+      const int64_t slice = ((int64_t)1 << 31) / lanes;  // edges of a launch
+      for (int64_t first = 0; first < nk; first += slice) {
+        const int64_t end = std::min(nk, first + slice);
+        hipLaunchKernelGGL(weights, dim3(grid1((end - first) * lanes)), dim3(256), 0, s, feats, first, end, D, k, vec,
+                           sid, pos, d2, nrm, sig2, w);
+      }
     } else {
       // s_f: median feature distance over the directed pairs (d2 is reused
       // for the feature distances; sigma above is not needed)

@@ -277,12 +277,37 @@ void order_after_failed_diffusion() {
   }
 }
 
+// Threads of all launches of a kernel; no launch since op `at` is refused.
+uint64_t threads_of(const char* kernel, size_t at) {
+  uint64_t sum = 0;
+  for (size_t i = at; i < ops().size(); i++) {
+    if (ops()[i].kind != kLaunch) continue;
+    if (ops()[i].launched >= (1ull << 32)) fprintf(stderr, "%s\n", ops()[i].name.c_str());
+    CHECK(ops()[i].launched < (1ull << 32));
+    if (ops()[i].name.find(kernel) != std::string::npos) sum += ops()[i].size;
+  }
+  return sum;
+}
+
+// 2^28 edges with 16 lanes each (more than 128 channels).
+void edge_weight_launches() {
+  const int64_t n = 1 << 24, k = 16;
+  lv_scene* sc = make_scene(n, S1);
+  float* f = static_cast<float*>(device_mem(4 * (size_t)n * 129));
+  lv_graph* g = nullptr;
+  const size_t at = ops().size();
+  const lv_status st = lv_graph_build_knn(sc, f, 129, (int)k, nullptr, S1, &g);
+  CHECK(threads_of("edge_weights", at) >= (uint64_t)(n * k * 16));
+  CHECK(st == LV_OK);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> tests = {
       {"destroy_on_other_device", destroy_on_other_device},
       {"order_after_failed_diffusion", order_after_failed_diffusion},
+      {"edge_weight_launches", edge_weight_launches},
   };
   CHECK(argc == 2 && tests.count(argv[1]));
   tests.at(argv[1])();
