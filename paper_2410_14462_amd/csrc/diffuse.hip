@@ -4,6 +4,8 @@
 // s_t = 1 / ||g_t|| (0 for a zero channel) and, in the same pass, the squared
 // norms of y for step t+1.  CSR SpMM: a group of C lanes (C = channel width,
 // power of two <= 64) owns one row; lane c handles channels c, c + C, ...
+#include <algorithm>
+
 #include "lv_internal.h"
 
 namespace lv {
@@ -745,13 +747,15 @@ __global__ void invert_kernel(const uint32_t* __restrict__ perm, int64_t n, uint
 
 // New row r = old row perm[r], its columns renumbered; off[r] = new row start.
 // 16 lanes per row (one lane per row, its accesses a row apart from the next
-// lane's, took 1200 us for 1M rows of 23 edges, 16 lanes 161).
+// lane's, took 1200 us for 1M rows of 23 edges, 16 lanes 161); a launch takes the
+// rows from `first` on, as many as its grid has (fewer than 2^32 threads).
 template <typename VT>
 __global__ __launch_bounds__(256) void permute_csr_kernel(
     const int32_t* __restrict__ rp, const int32_t* __restrict__ col, const VT* __restrict__ val,
     const uint32_t* __restrict__ perm, const uint32_t* __restrict__ inv, const uint32_t* __restrict__ off,
-    int64_t n, int64_t nnz, int32_t* __restrict__ rp2, int32_t* __restrict__ col2, VT* __restrict__ val2) {
-  const int64_t r = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
+    int64_t first, int64_t n, int64_t nnz, int32_t* __restrict__ rp2, int32_t* __restrict__ col2,
+    VT* __restrict__ val2) {
+  const int64_t r = first + (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4);
   const int sub = threadIdx.x & 15;
   if (r > n) return;
   if (r == n) {
@@ -867,15 +871,18 @@ hipError_t launch_graph_reorder(const float4* p0, int64_t n, const int32_t* rp, 
   uint32_t* dummy = k0;  // seg_start / seg_len outputs of the scan (one view)
   e = scan_counts(deg, perm, n, 1, off, dummy, dummy + 1, totals, tmp, s);
   if (e != hipSuccess) return e;
-  const unsigned nr = (unsigned)((n + 1 + 15) / 16);  // 16 rows per block
-  if (vt == LV_F32)
-    hipLaunchKernelGGL(permute_csr_kernel<float>, dim3(nr), dim3(256), 0, s, rp, col,
-                       static_cast<const float*>(val), perm, inv, off, n, nnz, rp2, col2,
-                       static_cast<float*>(val2));
-  else
-    hipLaunchKernelGGL(permute_csr_kernel<uint16_t>, dim3(nr), dim3(256), 0, s, rp, col,
-                       static_cast<const uint16_t*>(val), perm, inv, off, n, nnz, rp2, col2,
-                       static_cast<uint16_t*>(val2));
+  const int64_t slice = (int64_t)1 << 27;  // rows of a launch
+  for (int64_t first = 0; first <= n; first += slice) {
+    const unsigned nr = (unsigned)((std::min(slice, n + 1 - first) + 15) / 16);  // 16 rows per block
+    if (vt == LV_F32)
+      hipLaunchKernelGGL(permute_csr_kernel<float>, dim3(nr), dim3(256), 0, s, rp, col,
+                         static_cast<const float*>(val), perm, inv, off, first, n, nnz, rp2, col2,
+                         static_cast<float*>(val2));
+    else
+      hipLaunchKernelGGL(permute_csr_kernel<uint16_t>, dim3(nr), dim3(256), 0, s, rp, col,
+                         static_cast<const uint16_t*>(val), perm, inv, off, first, n, nnz, rp2, col2,
+                         static_cast<uint16_t*>(val2));
+  }
   return hipGetLastError();
 }
 

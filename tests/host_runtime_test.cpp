@@ -220,7 +220,7 @@ lv_scene* make_scene(int64_t n, void* s) {
 lv_graph* make_graph(int n, int deg, void* s) {
   int32_t* rp = static_cast<int32_t*>(device_mem(4 * (size_t)(n + 1)));
   int32_t* col = static_cast<int32_t*>(device_mem(4 * (size_t)n * deg + 4));
-  for (int i = 0; i <= n; i++) rp[i] = i * deg;
+  for (int i = 0; i <= n && deg; i++) rp[i] = i * deg;  // reserved memory is 0
   lv_graph* g = nullptr;
   CHECK(lv_graph_create_csr(n, (int64_t)n * deg, rp, col, col, LV_F32, s, &g) == LV_OK);
   return g;
@@ -301,6 +301,18 @@ void edge_weight_launches() {
   CHECK(st == LV_OK);
 }
 
+// The locality order of 2^28 rows, 16 lanes each.
+void graph_order_launches() {
+  const int n = 1 << 28;
+  lv_scene* sc = make_scene(n, S1);
+  lv_graph* g = make_graph(n, 0, S1);
+  float* x = static_cast<float*>(device_mem(8 * (size_t)n));
+  const size_t at = ops().size();
+  const lv_status st = lv_diffuse(sc, g, x, LV_F32, 1, 1, x + n, S1);
+  CHECK(threads_of("permute_csr", at) >= 16 * ((uint64_t)n + 1));
+  CHECK(st == LV_OK);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -308,6 +320,7 @@ int main(int argc, char** argv) {
       {"destroy_on_other_device", destroy_on_other_device},
       {"order_after_failed_diffusion", order_after_failed_diffusion},
       {"edge_weight_launches", edge_weight_launches},
+      {"graph_order_launches", graph_order_launches},
   };
   CHECK(argc == 2 && tests.count(argv[1]));
   tests.at(argv[1])();
