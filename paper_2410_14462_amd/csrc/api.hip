@@ -924,6 +924,10 @@ lv_status lv_uplift_accumulate_sets(const lv_camera* cams, int32_t m, const lv_f
   const int64_t budget = chunk_budget_bytes(&ws);
   int64_t mc = std::max<int64_t>(1, std::min<int64_t>(m, budget / per_view));
   mc = std::min<int64_t>(mc, 1 << (31 - kViewShift));
+  int64_t tiles = 1;  // of the largest view
+  for (int v = 0; v < m; v++)
+    tiles = std::max<int64_t>(tiles, (int64_t)((cams[v].width + kTile - 1) / kTile) * ((cams[v].height + kTile - 1) / kTile));
+  mc = std::min(mc, kMaxBlendTiles / tiles);
   for (int v0 = 0; v0 < m;) {
     int mv = (int)std::min<int64_t>(mc, m - v0);
     const uint32_t* ids = nullptr;

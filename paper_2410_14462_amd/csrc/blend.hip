@@ -1185,7 +1185,7 @@ hipError_t launch_blend_t(const BlendArgs& a, int m, hipStream_t s) {
   const bool multi = a.ngroups > 1;
   int64_t work = (int64_t)a.tiles_stride * m;
   int64_t blocks = (work + 7) / 8 * 32;
-  const bool two = a.max_width > 32 || 4 * work <= kFewQuadrants;
+  const bool two = a.max_width > 32 || 4 * work <= kFewQuadrants;  // one wave holds 32 channels at most
   if (multi) {
     // one wave per half tile: two per tile, whole rounds of 8 XCDs
     const int64_t pblocks = ((int64_t)a.tiles_stride * m + 7) / 8 * 16;

@@ -254,6 +254,9 @@ struct BlendArgs {
   int32_t max_width;           // widest group; 0: tail channels only
   int32_t has_tail;            // the last group has tail channels
 };
+// m tiles_stride <= kMaxBlendTiles (four quadrants of up to 128 threads each: a
+// grid holds fewer than 2^32 threads).
+constexpr int64_t kMaxBlendTiles = ((int64_t)1 << 23) - 8;
 hipError_t launch_blend(const BlendArgs& a, lv_dtype dtype, int m, hipStream_t s);
 // dst_beta[k][i] += beta[i], dst_counts[k][i] += counts[i] (entries may be
 // NULL) for the k < nd members of a class of feature sets that take the same

@@ -313,6 +313,21 @@ void graph_order_launches() {
   CHECK(st == LV_OK);
 }
 
+// 2048 views of 1920x1080 in one group of more than 32 channels: two waves for
+// each of 67M quadrants.
+void uplift_launches() {
+  const int m = 2048, D = 33, n = 10;
+  lv_scene* sc = make_scene(n, S1);
+  lv_camera cam = {{1, 0, 0, 0, 1, 0, 0, 0, 1}, {0, 0, 0}, 1000, 1000, 960, 540, 0.01f, 1920, 1080, 0};
+  std::vector<lv_camera> cams(m, cam);
+  std::vector<const void*> maps(m, device_mem(64));
+  float* out = static_cast<float*>(device_mem(4 * n * D + 4 * (size_t)m * D));
+  const size_t at = ops().size();
+  const lv_status st = lv_uplift(sc, cams.data(), m, maps.data(), LV_FP8_E4M3, out + n * D, D, out, nullptr, S1);
+  CHECK(threads_of("blend_wide", at) >= (uint64_t)m * 120 * 68 * 4 * 64);
+  CHECK(st == LV_OK);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -321,6 +336,7 @@ int main(int argc, char** argv) {
       {"order_after_failed_diffusion", order_after_failed_diffusion},
       {"edge_weight_launches", edge_weight_launches},
       {"graph_order_launches", graph_order_launches},
+      {"uplift_launches", uplift_launches},
   };
   CHECK(argc == 2 && tests.count(argv[1]));
   tests.at(argv[1])();
