@@ -406,7 +406,7 @@ lv_status lv_graph_csr(const lv_graph* graph, int64_t* n, int64_t* nnz, int32_t*
  * g0 and out are device [n][D] of dtype (LV_F32 or LV_BF16; sums and norms
  * are FP32).  out = g_steps (steps = 0 copies g0).  scene may be NULL; if
  * given, its size must equal the graph's.  Scratch: 2 n D signal elements
- * (4 n D with a scene) and, per step, the D norms in up to 64 copies. */
+ * (4 n D with a scene) and at most 1 MB of norms. */
 lv_status lv_diffuse(const lv_scene* scene, const lv_graph* graph, const void* g0, lv_dtype dtype,
                      int32_t D, int32_t steps, void* out, void* stream);
 

@@ -45,6 +45,11 @@ inline int norm_slots(int D) {
   return s;
 }
 
+// The norms of the last steps: step t divides by row t mod kNormRows and adds to
+// the next one; half of the rows are cleared at a time, before the first of them
+// is added to again, while the row that is read lies in the other half.
+constexpr int kNormRows = 64;
+
 // Sum over the slots of channel ch, the same in every block (a fixed order);
 // threads t, t + C, ... of the block's 256 hold the same channel, C a power of
 // two up to 64.  A thread loads T of its 64 C / 256 slots at a time: one after
@@ -611,7 +616,7 @@ hipError_t diffuse_t(const int32_t* rp, const int32_t* col, const void* val, lv_
   }
   const int slots = norm_slots(D);
   const size_t row = (size_t)D * slots;  // the norms of one step
-  hipError_t e = hipMemsetAsync(norms, 0, sizeof(float) * row * (size_t)(steps + 1), s);
+  hipError_t e = hipMemsetAsync(norms, 0, sizeof(float) * diffuse_norm_floats(D, steps), s);
   if (e != hipSuccess) return e;
   if (total == 0) return hipSuccess;
   if (D <= 64) {
@@ -626,10 +631,14 @@ hipError_t diffuse_t(const int32_t* rp, const int32_t* col, const void* val, lv_
   const void* cur = g0;
   for (int t = 0; t < steps; t++) {
     void* dst = (t == steps - 1) ? out : ((t & 1) ? b1 : b0);
-    e = vt == LV_F32 ? spmm_dispatch<GT, LV_F32>(rp, col, val, n, D, cur, norms + t * row, slots, dst,
-                                                 norms + (t + 1) * row, s)
-                     : spmm_dispatch<GT, LV_BF16>(rp, col, val, n, D, cur, norms + t * row, slots, dst,
-                                                  norms + (t + 1) * row, s);
+    const float* const nin = norms + t % kNormRows * row;
+    float* const nout = norms + (t + 1) % kNormRows * row;
+    if (t + 1 >= kNormRows && (t + 1) % (kNormRows / 2) == 0) {
+      e = hipMemsetAsync(nout, 0, sizeof(float) * row * (kNormRows / 2), s);
+      if (e != hipSuccess) return e;
+    }
+    e = vt == LV_F32 ? spmm_dispatch<GT, LV_F32>(rp, col, val, n, D, cur, nin, slots, dst, nout, s)
+                     : spmm_dispatch<GT, LV_BF16>(rp, col, val, n, D, cur, nin, slots, dst, nout, s);
     if (e != hipSuccess) return e;
     cur = dst;
   }
@@ -788,7 +797,9 @@ __global__ void permute_rows_kernel(const T* __restrict__ src, T* __restrict__ d
 
 }  // namespace
 
-size_t diffuse_norm_floats(int D, int steps) { return (size_t)D * norm_slots(D) * (size_t)(steps + 1); }
+size_t diffuse_norm_floats(int D, int steps) {
+  return (size_t)D * norm_slots(D) * (size_t)(steps < kNormRows ? steps + 1 : kNormRows);
+}
 
 hipError_t launch_diffuse(const int32_t* row_ptr, const int32_t* col, const void* val,
                           lv_dtype val_dtype, int64_t n, const void* g0, lv_dtype dtype, int D,

@@ -328,6 +328,17 @@ void uplift_launches() {
   CHECK(st == LV_OK);
 }
 
+// The device memory of a diffusion does not grow with its steps.
+void diffusion_memory() {
+  const int n = 64, D = 64;
+  lv_graph* g = make_graph(n, 2, S1);
+  float* x = static_cast<float*>(device_mem(8 * n * D));
+  g_peak = g_bytes;
+  const uint64_t held = g_bytes;
+  CHECK(lv_diffuse(nullptr, g, x, LV_F32, D, 100000, x + n * D, S1) == LV_OK);
+  CHECK(g_peak - held < (4 << 20));
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -337,6 +348,7 @@ int main(int argc, char** argv) {
       {"edge_weight_launches", edge_weight_launches},
       {"graph_order_launches", graph_order_launches},
       {"uplift_launches", uplift_launches},
+      {"diffusion_memory", diffusion_memory},
   };
   CHECK(argc == 2 && tests.count(argv[1]));
   tests.at(argv[1])();

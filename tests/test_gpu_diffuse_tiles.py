@@ -35,3 +35,28 @@ def test_forms_and_tiles(D, n, sdt):
     ref = od.diffuse(od.csr_matrix(n, rp, col, val), g0.float().numpy().astype(np.float64), 1)
     tol = (hub + 100) * 2.0 ** -24 + (2.0 ** -8 if sdt == "bf16" else 0.0)
     assert np.all(np.abs(out - ref) <= tol * np.abs(ref))
+
+
+@pytest.mark.parametrize("D", [1, 16, 37])
+@pytest.mark.parametrize("steps", [63, 64, 95, 96, 97, 130])
+def test_more_steps_than_norm_rows(steps, D):
+    # 64 rows of norms are used in turn; positive terms, so a step is off by at
+    # most (terms in a chain) 2^-24 relatively (rows that feed on themselves alone
+    # may die out: below 1e-37 FP32 is no longer normal)
+    n, hub = 300, 40
+    rp, col, val = ragged_graph(n, 5, hub)
+    rp, col, val = with_self_loops(n, rp, col, val)
+    g0 = np.random.default_rng(D).uniform(0.1, 1.0, (n, D)).astype(np.float32)
+    G = lv.Graph(*(torch.as_tensor(x, device="cuda") for x in (rp, col, val)))
+    out = G.diffuse(torch.as_tensor(g0, device="cuda"), steps).cpu().numpy().astype(np.float64)
+    ref = od.diffuse(od.csr_matrix(n, rp, col, val), g0.astype(np.float64), steps)
+    assert np.all(np.abs(out - ref) <= steps * (hub + 100) * 2.0 ** -24 * np.abs(ref) + 1e-37)
+
+
+def with_self_loops(n, rp, col, val):
+    """One more edge of weight 1 per row, to itself: no signal dies out."""
+    deg = np.diff(rp)
+    rp2 = np.concatenate([[0], np.cumsum(deg + 1)]).astype(np.int32)
+    col2 = np.insert(col, rp[1:], np.arange(n)).astype(np.int32)
+    val2 = np.insert(val, rp[1:], 1.0).astype(np.float32)
+    return rp2, col2, val2
