@@ -105,8 +105,9 @@ const char* lv_last_error(void);
 
 /* ------------------------------------------------------- device memory -- */
 /* Every device buffer the library allocates -- cached scratch (structure
- * builds, pair buffers), temporary scratch (graph builds, filtering, server
- * accumulators) and the buffers its handles own -- comes from `alloc` and
+ * builds, pair buffers, graph builds and orders), temporary scratch
+ * (filtering, server accumulators, graph builds of more than the scratch
+ * budget) and the buffers its handles own -- comes from `alloc` and
  * returns through `free` once registered (e.g. a framework's caching
  * allocator); without one, hipMalloc / hipFree (hipMallocAsync /
  * hipFreeAsync for temporary scratch).  alloc(bytes, stream, ctx) returns a
@@ -123,7 +124,8 @@ typedef void* (*lv_alloc_fn)(size_t bytes, void* stream, void* ctx);
 typedef void (*lv_free_fn)(void* ptr, size_t bytes, void* stream, void* ctx);
 lv_status lv_set_allocator(lv_alloc_fn alloc, lv_free_fn free, void* ctx);
 /* Frees the scratch the library caches for `stream` (all_streams != 0: for
- * every stream, and the buffers kept from destroyed scenes); the scratch is
+ * every stream, and the buffers kept from destroyed scenes and graphs, at
+ * most 24 and 1 GiB); the scratch is
  * allocated again by the next call that needs it.  No library work may be in
  * flight on those streams. */
 lv_status lv_release_scratch(void* stream, int32_t all_streams);
@@ -368,10 +370,10 @@ lv_status lv_graph_destroy(lv_graph* graph);
  * directed weight where both directions exist; the union pairs with a
  * positive weight are stored, columns ascending; rows are normalised to sum
  * 1 (FP32 values) and a row without any gets a self-loop of weight 1.
- * feats: device FP32 [n][D] (e.g. uplifted features).  Scratch (about
- * 90 + 48 k bytes per Gaussian) is the stream's, kept until lv_release_scratch; the
- * call synchronises the stream once (to size the CSR).  Errors:
- * LV_ERR_INVALID_ARG (k outside [1, 32], D outside [1, 4096], n <= k, null
+ * feats: device FP32 [n][D] (e.g. uplifted features).  Scratch: about
+ * 90 + 48 k bytes per Gaussian, cached per stream until lv_release_scratch up
+ * to the scratch budget of lv_uplift, temporary above it; the call
+ * synchronises the stream once (to size the CSR).  Errors: LV_ERR_INVALID_ARG (k outside [1, 32], D outside [1, 4096], n <= k, null
  * pointers), LV_ERR_UNSUPPORTED (n (2k + 1) >= 2^31), LV_ERR_OUT_OF_MEMORY,
  * LV_ERR_DEVICE. */
 typedef enum lv_graph_kind {

@@ -186,6 +186,29 @@ int64_t chunk_budget_bytes(const Workspace* ws = nullptr) {
   return b;
 }
 
+// Scratch of a graph build or order: the stream's, kept for the next one, up to
+// the budget of the structure builds' scratch; above it from the stream-ordered
+// allocator, given back when the call's work ends.
+struct GraphScratch {
+  Workspace& ws;
+  hipStream_t s;
+  void* p = nullptr;
+  size_t temp = 0;
+  hipError_t ensure(size_t bytes) {
+    if (bytes <= (size_t)4 << 30 || (int64_t)bytes <= chunk_budget_bytes(&ws)) {
+      const hipError_t e = ws.graph.ensure(bytes, s);
+      p = ws.graph.p;
+      return e;
+    }
+    const hipError_t e = lv::dev_alloc(&p, bytes, s, true);
+    if (e == hipSuccess) temp = bytes;
+    return e;
+  }
+  ~GraphScratch() {
+    if (temp) lv::dev_free(p, temp, s, true);
+  }
+};
+
 }  // namespace
 
 struct lv_scene {
@@ -1363,10 +1386,11 @@ lv_status lv_graph_build_knn(lv_scene* sc, const float* feats, int32_t D, int32_
   {
     Workspace& ws = *workspace_for(s);
     std::lock_guard<std::mutex> lk(ws.mu);
+    GraphScratch scratch{ws, s};
     GraphAlloc alloc;
     alloc.scratch = [&](void** p, size_t bytes) {
-      const hipError_t r = ws.graph.ensure(bytes, s);
-      *p = ws.graph.p;
+      const hipError_t r = scratch.ensure(bytes);
+      *p = scratch.p;
       return r;
     };
     alloc.csr = [&](int64_t nnz, int32_t** r, int32_t** c, float** v) {
@@ -1453,7 +1477,8 @@ lv_status lv_diffuse(const lv_scene* sc, const lv_graph* gc, const void* g0, lv_
     const int64_t n = g->n, nnz = g->nnz;
     Workspace& ws = *workspace_for(s);
     std::lock_guard<std::mutex> wlk(ws.mu);
-    HIP_TRY(ws.graph.ensure(4 * reorder_scratch_words(n), s));
+    GraphScratch scratch{ws, s};
+    HIP_TRY(scratch.ensure(4 * reorder_scratch_words(n)));
     hipError_t e = grow(g->perm, 4 * (size_t)n);
     if (e == hipSuccess) e = grow(g->inv, 4 * (size_t)n);
     if (e == hipSuccess) e = grow(g->rp2, 4 * (size_t)(n + 1));
@@ -1461,7 +1486,7 @@ lv_status lv_diffuse(const lv_scene* sc, const lv_graph* gc, const void* g0, lv_
     if (e == hipSuccess) e = grow(g->val2, dtype_size(g->val_dtype) * (size_t)(nnz + 1));
     if (e == hipSuccess)
       e = launch_graph_reorder(sc->caller_p0(), n, g->row_ptr.as<int32_t>(), g->col.as<int32_t>(),
-                               g->val.p, g->val_dtype, nnz, ws.graph.as<uint32_t>(),
+                               g->val.p, g->val_dtype, nnz, static_cast<uint32_t*>(scratch.p),
                                g->perm.as<uint32_t>(), g->inv.as<uint32_t>(), g->rp2.as<int32_t>(),
                                g->col2.as<int32_t>(), g->val2.p, s);
     if (e != hipSuccess) return fail(LV_ERR_DEVICE, "graph order: %s", hipGetErrorString(e));

@@ -339,6 +339,23 @@ void diffusion_memory() {
   CHECK(g_peak - held < (4 << 20));
 }
 
+// The scratch of a graph build stays with the stream up to the scratch budget
+// (16 GiB on this card) and is given back above it.
+void graph_scratch() {
+  for (int64_t n : {(int64_t)1 << 20, (int64_t)1 << 25}) {
+    lv_scene* sc = make_scene(n, S1);
+    float* f = static_cast<float*>(device_mem(4 * (size_t)n));
+    lv_graph* g = nullptr;
+    g_peak = g_bytes;
+    const uint64_t held = g_bytes;
+    CHECK(lv_graph_build_knn(sc, f, 1, 16, nullptr, S1, &g) == LV_OK);
+    CHECK(g_peak - held >= 800 * (uint64_t)n);
+    CHECK(g_bytes - held <= ((uint64_t)18 << 30));
+    CHECK((g_bytes - held >= 800 * (uint64_t)n) == (n == 1 << 20));
+    CHECK(lv_graph_destroy(g) == LV_OK && lv_scene_destroy(sc) == LV_OK && lv_release_scratch(S1, 0) == LV_OK);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -349,6 +366,7 @@ int main(int argc, char** argv) {
       {"graph_order_launches", graph_order_launches},
       {"uplift_launches", uplift_launches},
       {"diffusion_memory", diffusion_memory},
+      {"graph_scratch", graph_scratch},
   };
   CHECK(argc == 2 && tests.count(argv[1]));
   tests.at(argv[1])();

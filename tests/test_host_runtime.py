@@ -10,7 +10,7 @@ import paper_2410_14462_amd as lv
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 TESTS = ["destroy_on_other_device", "order_after_failed_diffusion", "edge_weight_launches",
-         "graph_order_launches", "uplift_launches", "diffusion_memory"]
+         "graph_order_launches", "uplift_launches", "diffusion_memory", "graph_scratch"]
 
 
 @pytest.fixture(scope="module")
