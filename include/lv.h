@@ -373,7 +373,8 @@ lv_status lv_graph_destroy(lv_graph* graph);
  * feats: device FP32 [n][D] (e.g. uplifted features).  Scratch: about
  * 90 + 48 k bytes per Gaussian, cached per stream until lv_release_scratch up
  * to the scratch budget of lv_uplift, temporary above it; the call
- * synchronises the stream once (to size the CSR).  Errors: LV_ERR_INVALID_ARG (k outside [1, 32], D outside [1, 4096], n <= k, null
+ * synchronises the stream once (to size the CSR).  Errors:
+ * LV_ERR_INVALID_ARG (k outside [1, 32], D outside [1, 4096], n <= k, null
  * pointers), LV_ERR_UNSUPPORTED (n (2k + 1) >= 2^31), LV_ERR_OUT_OF_MEMORY,
  * LV_ERR_DEVICE. */
 typedef enum lv_graph_kind {

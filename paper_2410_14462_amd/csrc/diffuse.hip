@@ -320,18 +320,24 @@ __global__ __launch_bounds__(256) void spmm_rows_kernel(const int32_t* __restric
   }
 }
 
+// Edges that a wave of spmm_wide_kernel stages in a round.
+template <int D, int C>
+constexpr int spmm_wide_edges() {
+  return 64 * C / D > 32 ? 16 * (64 * C / D) : 512;
+}
+
 // D = 8, 16, 32 or 64 channels in rows of pieces of C channels, one load each (4
 // channels in FP32, 8 in BF16: 16 bytes; 4 in small graphs), one piece per lane,
 // L = D / C lanes per row, R = 64 / L consecutive rows per wave, whose edges are
-// one contiguous range.  The wave takes that range E edges at a time: columns and weights are read coalesced and
-// left in LDS as (row offset, weight); each row's lanes then walk the row's part,
-// U gathers in flight, and sum in edge order with the same fused multiply-adds as
-// spmm_kernel.
+// one contiguous range.  The wave takes that range E edges at a time: columns and
+// weights are read coalesced and left in LDS as (row offset, weight); each row's
+// lanes then walk the row's part, U gathers in flight, and sum in edge order with
+// the same fused multiply-adds as spmm_kernel.
 // What bounds a step is instructions and latency before bandwidth: with four
 // channels per lane, edges broadcast by shuffles and a block per 16 rows, each
 // gather cost a BF16 lane 13 instructions for 4 channels (now about 18 for 8), and
 // every block began with the norms, the row pointers and the edges one after the
-// other.  The blocks now stay (kSpmmWideBlocks), and a tile's edges and the next
+// other.  The blocks now stay (spmm_wide_blocks), and a tile's edges and the next
 // one's row pointers are loaded while the tile before is summed.  U = 4: of 4, 6,
 // 8 and 12 gathers in flight 4 is the fastest or level everywhere (D = 64 in
 // FP32, 1M rows: 252, 269, 272, 303 us a step).  Steps, 16 edges a row, before and
@@ -352,7 +358,7 @@ __global__ __launch_bounds__(256) void spmm_wide_kernel(const int32_t* __restric
   constexpr int L = D / C, R = 64 / L;
   constexpr int kPiece = C * (GT == LV_F32 ? 4 : 2), kWords = kPiece / 4;  // bytes and words of a lane's piece of a row
   typedef uint32_t piece_t __attribute__((ext_vector_type(kWords)));
-  constexpr int E = R > 32 ? 16 * R : 512, P = R < 32 ? 4 : 8;  // edges per round, per lane and load
+  constexpr int E = spmm_wide_edges<D, C>(), P = R < 32 ? 4 : 8;  // edges per round, per lane and load
   constexpr uint32_t kRowBytes = D * (GT == LV_F32 ? 4 : 2);
   __shared__ union {
     uint2 edge[4][E];
@@ -535,8 +541,14 @@ hipError_t spmm_launch(const int32_t* rp, const int32_t* col, const void* val, i
 
 // Five blocks per CU, all resident, sweep the rows in order: 1024, 1280, 1536 and
 // 2048 blocks take 162, 144, 138 and 172 us a step (1M rows, D = 64, 16 edges a
-// row, BF16) and 262, 252, 260 and 293 in FP32.
-constexpr int64_t kSpmmWideBlocks = 1280;
+// row, BF16) and 262, 252, 260 and 293 in FP32.  Where the staged edges leave room
+// for four (D = 8 in BF16), four: 1M rows 50.2 us, 61.0 with a fifth in a round of
+// its own.
+template <int D, int C>
+constexpr int64_t spmm_wide_blocks() {
+  constexpr int lds = std::max(4 * 8 * spmm_wide_edges<D, C>(), 4 * 256 * C) + 4 * D;
+  return 256 * std::min(5, 160 * 1024 / lds);
+}
 
 // Up to this many tiles the small form of spmm_wide_kernel runs (C = 4, U = 8).
 // Steps of 18 edges a row, small / large form: D = 64, 5,000 rows (313 tiles) FP32
@@ -554,7 +566,7 @@ hipError_t spmm_wide_launch(const int32_t* rp, const int32_t* col, const void* v
   const int rows = 256 * (few ? 4 : C) / D;  // per tile
   const int64_t tiles = (n + rows - 1) / rows;
   const int64_t want = (tiles + 7) / 8 * 8;
-  const unsigned blocks = (unsigned)(want < kSpmmWideBlocks ? want : kSpmmWideBlocks);
+  const unsigned blocks = (unsigned)std::min(want, spmm_wide_blocks<D, C>());
   const bool big = n * D * (GT == LV_F32 ? 4 : 2) > (int64_t)1 << 32;
   hipLaunchKernelGGL((few   ? spmm_wide_kernel<D, 4, 8, GT, VT, false>
                       : big ? spmm_wide_kernel<D, C, 4, GT, VT, true>
