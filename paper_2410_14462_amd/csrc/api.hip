@@ -1015,6 +1015,7 @@ lv_status lv_uplift_accumulate_sets(const lv_camera* cams, int32_t m, const lv_f
     ba.sets = reinterpret_cast<const SetDesc*>(dev);
     ba.groups = reinterpret_cast<const ChanGroup*>(dev + b_sets);
     ba.ngroups = (int32_t)groups.size();
+    ba.pairs = P;
     ba.max_width = max_width;
     ba.has_tail = !groups.empty() && groups.back().ntail > 0 ? 1 : 0;
     {

@@ -230,6 +230,14 @@ __device__ __forceinline__ void lds_barrier() {
 // 60, 2 views 81 / 90.
 constexpr int64_t kFewQuadrants = 4096;
 
+// Mean length of the tiles' lists from which a group of more than 32 channels gets
+// two waves also where the launch fills the chip: with short lists the second wave
+// takes room and its start is most of what it does.  Call with 20 views of 800x600,
+// D = 64, one wave / two: lists of 6 in FP32 454 / 618 us, in BF16 414 / 642; of 23
+// 598 / 735 and 563 / 770; of 87 1382 / 1398 and 1361 / 1388; of 289 2874 / 2868 and
+// 2881 / 2863; of 1154 (10 views) 2199 / 2191 and 2207 / 2154.
+constexpr int64_t kLongLists = 128;
+
 // Orders one wave's LDS accesses.
 __device__ __forceinline__ void lds_order() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -520,15 +528,12 @@ __device__ __forceinline__ void batch_mfma(bool two, uint32_t rows, const float*
   }
 }
 
-// Rows [0, count) of a batch, count <= 32.
-__device__ __forceinline__ uint32_t first_rows(int count) { return count < 32 ? (1u << count) - 1u : ~0u; }
-
 // One atomic per (queued Gaussian, channel): D row m of the batch is ring
-// row m, whose Gaussian id lane m holds; live: the rows that are added.  FP8
-// maps: the products were formed on the codes, the channel's scale multiplies
-// them here.
-template <lv_dtype DT, bool FIX>
-__device__ __forceinline__ void batch_scatter_t(const GroupLanes& L, bool two, uint32_t live,
+// row m, whose Gaussian id lane m holds.  rows: how many rows are added, or
+// (kMask) which.  FP8 maps: the products were formed on the codes, the
+// channel's scale multiplies them here.
+template <lv_dtype DT, bool FIX, bool kMask>
+__device__ __forceinline__ void batch_scatter_t(const GroupLanes& L, bool two, uint32_t rows,
                                                 uint32_t ring_gid, int lane, f32x16 acc0,
                                                 f32x16 acc1) {
   if constexpr (DT == LV_FP8_E4M3) {
@@ -536,15 +541,16 @@ __device__ __forceinline__ void batch_scatter_t(const GroupLanes& L, bool two, u
     acc1 *= L.srcsc[1];
   }
   const bool upper = lane >= 32;
-  const uint32_t mine = upper ? live >> 4 : live;
+  const int count = (int)rows;
+  const uint32_t mine = upper ? rows >> 4 : rows;
 #pragma unroll
   for (int r = 0; r < 16; r++) {
     const int m0 = 8 * (r >> 2) + (r & 3), m1 = m0 + 4;
-    if ((live >> m0) & 0x11u) {  // wave-uniform
+    if (kMask ? ((rows >> m0) & 0x11u) != 0u : m0 < count) {  // wave-uniform
       const uint32_t g0 = (uint32_t)__builtin_amdgcn_readlane((int)ring_gid, m0);
       const uint32_t g1 = (uint32_t)__builtin_amdgcn_readlane((int)ring_gid, m1);
       const int64_t gid = (int64_t)(upper ? g1 : g0);
-      if ((mine >> m0) & 1u) {
+      if (kMask ? ((mine >> m0) & 1u) != 0u : (upper ? m1 : m0) < count) {
         if (L.outp[0] && acc0[r] != 0.0f) u_atomic_add(L.outp[0], gid * L.outD[0], acc0[r], FIX);
         if (two && L.outp[1] && acc1[r] != 0.0f) u_atomic_add(L.outp[1], gid * L.outD[1], acc1[r], FIX);
       }
@@ -554,14 +560,14 @@ __device__ __forceinline__ void batch_scatter_t(const GroupLanes& L, bool two, u
 
 // fixed (a deterministic accumulator) is wave-uniform: one branch per
 // flush, each side a straight run of atomics
-template <lv_dtype DT>
-__device__ __forceinline__ void batch_scatter(const GroupLanes& L, bool two, uint32_t live,
+template <lv_dtype DT, bool kMask = false>
+__device__ __forceinline__ void batch_scatter(const GroupLanes& L, bool two, uint32_t rows,
                                               uint32_t ring_gid, int lane, f32x16 acc0,
                                               f32x16 acc1, bool fixed) {
   if (fixed)
-    batch_scatter_t<DT, true>(L, two, live, ring_gid, lane, acc0, acc1);
+    batch_scatter_t<DT, true, kMask>(L, two, rows, ring_gid, lane, acc0, acc1);
   else
-    batch_scatter_t<DT, false>(L, two, live, ring_gid, lane, acc0, acc1);
+    batch_scatter_t<DT, false, kMask>(L, two, rows, ring_gid, lane, acc0, acc1);
 }
 
 // One channel group (at most 64 + 4 channels), one workgroup per (view,
@@ -571,22 +577,27 @@ __device__ __forceinline__ void batch_scatter(const GroupLanes& L, bool two, uin
 // walks and fills two queues of 32 rows in turn, the second flushes the one just
 // filled, and they meet at one barrier per queue, which neither loads nor atomics
 // in flight hold up; else one wave does both with one queue.  Two waves where
-// the launch has few quadrants (kFewQuadrants) or the group more than 32
-// channels, whose flush is long.  Launch, the walk before blend_step / one wave /
-// two: 200k Gaussians, 50 views of 512x384, D = 64 in BF16 3.57 / 3.52 / 3.42 ms
-// (the atomics' rate bounds it), D = 1 1.84 / 1.45 / 1.94; 20 views, D = 32 in
-// FP32 1.04 / 0.98 / 0.96, in BF16 1.05 / 1.02 / 0.92; 20k Gaussians, 20 views of
-// 800x600, D = 32 in FP32 0.99 / 0.88 / 1.08, D = 16 0.95 / 0.83 / 1.03; 10k
-// Gaussians, 4 views of 128x128, D = 8 165 / 133 / 82 us; 50k Gaussians, nine
-// launches of a 333x251 view, D = 37 455 / 445 / 390 us.  Occupancy: waves per SIMD the register
-// allocation must allow.  BF16 maps need no low operand halves, so they fit four.
-template <lv_dtype DT>
+// the launch has few quadrants (kFewQuadrants), or where the group has more than
+// 32 channels, whose flush is long, and the lists are long (kLongLists).  Launch,
+// the walk before blend_step / one wave / two: 200k Gaussians, 50 views of
+// 512x384, D = 64 in BF16 3.57 / 3.52 / 3.42 ms (the atomics' rate bounds it),
+// D = 1 1.84 / 1.45 / 1.94; 20 views, D = 32 in FP32 1.04 / 0.98 / 0.96, in BF16
+// 1.05 / 1.02 / 0.92; 20k Gaussians, 20 views of 800x600, D = 32 in FP32 0.99 /
+// 0.88 / 1.08, D = 16 0.95 / 0.83 / 1.03; 10k Gaussians, 4 views of 128x128, D = 8
+// 165 / 133 / 82 us; 50k Gaussians, nine launches of a 333x251 view, D = 37 455 /
+// 445 / 390 us.
+// kBlocks: blocks of 32 channels that the registers hold, 1 where the group has
+// no more.  Occupancy: waves per SIMD the register allocation must allow.  BF16
+// maps need no low operand halves, so they fit four, except that one wave with
+// two blocks from HWC maps spills then (20 views of 800x600, 2000 Gaussians,
+// D = 64: 527 us with four, 414 with three).
+template <lv_dtype DT, bool PX, bool kTwo, int kBlocks>
 constexpr int wide_waves() {
-  return DT == LV_BF16 ? 4 : 3;
+  return DT == LV_BF16 && (PX || kTwo || kBlocks == 1) ? 4 : 3;
 }
 
-template <lv_dtype DT, bool PX, bool kTwo>
-__global__ __launch_bounds__(kTwo ? 128 : 64, (wide_waves<DT>())) void blend_wide_kernel(
+template <lv_dtype DT, bool PX, bool kTwo, int kBlocks>
+__global__ __launch_bounds__(kTwo ? 128 : 64, (wide_waves<DT, PX, kTwo, kBlocks>())) void blend_wide_kernel(
     const Rec* __restrict__ rec, const uint32_t* __restrict__ ids, const uint2* __restrict__ ranges,
     const ViewGeom* __restrict__ geom, int64_t n, int tiles_stride, int nviews,
     const SetDesc* __restrict__ sets, const ChanGroup* __restrict__ groups, int ngroups) {
@@ -661,10 +672,10 @@ __global__ __launch_bounds__(kTwo ? 128 : 64, (wide_waves<DT>())) void blend_wid
     {
       const ChanGroup& grp = groups[q.cg];
       const bool takes = group_lanes<DT>(grp, sets, q, lane, L1);
-      two1 = kTwo && grp.width > 32;  // one wave: groups of up to 32 channels only
+      two1 = kBlocks == 2 && grp.width > 32;
       if (takes) {
 #pragma unroll
-        for (int b = 0; b < (kTwo ? 2 : 1); b++)
+        for (int b = 0; b < kBlocks; b++)
 #pragma unroll
           for (int t = 0; t < 4; t++)
             load_row8<DT, PX>(L1, b, q.qy + 2 * t + (lane >> 5), q.qx, q.g, fh[b][t], fl[b][t]);
@@ -733,13 +744,13 @@ __global__ __launch_bounds__(kTwo ? 128 : 64, (wide_waves<DT>())) void blend_wid
     // not 0).  The others are zeros and are not added: their products are zero
     // only where the features are finite, and a Gaussian that no pixel counts
     // takes nothing from the view, whatever the map holds there.
-    const uint32_t live = (uint32_t)__ballot(bs != 0.0f) & first_rows(count);
+    const uint32_t live = (uint32_t)__ballot(bs != 0.0f && lane < count);
     if (has_main) {
       const uint32_t rows = row_bits(pix);
       const float* wrow = Wt + (lane & 31) * kWtPitch + 8 * (lane >> 5);
       f32x16 acc0 = {}, acc1 = {};
       batch_mfma<kSplitF>(two1, rows, wrow, fh, fl, acc0, acc1);
-      batch_scatter<DT>(L1, two1, live, ring_gid, lane, acc0, acc1, fixedU);
+      batch_scatter<DT, true>(L1, two1, live, ring_gid, lane, acc0, acc1, fixedU);
     }
   };
   // statistics go to every set whose statistics this work item takes
@@ -1042,7 +1053,7 @@ __global__ __launch_bounds__(64, 2) void blend_pair_kernel(
             }
           }
         }
-        if (pend) batch_scatter<DT>(Lp, twop, first_rows(count), ring_gid, lane, acc0, acc1, fixedU);
+        if (pend) batch_scatter<DT>(Lp, twop, count, ring_gid, lane, acc0, acc1, fixedU);
         pend = false;
         if (!ok) continue;
         acc0 = f32x16{};
@@ -1074,7 +1085,7 @@ __global__ __launch_bounds__(64, 2) void blend_pair_kernel(
         twop = two;
         pend = true;
       }
-      if (pend) batch_scatter<DT>(Lp, twop, first_rows(count), ring_gid, lane, acc0, acc1, fixedU);
+      if (pend) batch_scatter<DT>(Lp, twop, count, ring_gid, lane, acc0, acc1, fixedU);
     } else {
       for (int cg = 0; cg < ngroups; cg++) {
         if (!((gmask >> cg) & 1u)) continue;
@@ -1115,7 +1126,7 @@ __global__ __launch_bounds__(64, 2) void blend_pair_kernel(
             }
           }
         }
-        batch_scatter<DT>(L, two, first_rows(count), ring_gid, lane, acc0, acc1, fixedU);
+        batch_scatter<DT>(L, two, count, ring_gid, lane, acc0, acc1, fixedU);
       }
     }
     __syncthreads();  // rows read before they are written again
@@ -1185,7 +1196,7 @@ hipError_t launch_blend_t(const BlendArgs& a, int m, hipStream_t s) {
   const bool multi = a.ngroups > 1;
   int64_t work = (int64_t)a.tiles_stride * m;
   int64_t blocks = (work + 7) / 8 * 32;
-  const bool two = a.max_width > 32 || 4 * work <= kFewQuadrants;  // one wave holds 32 channels at most
+  const bool two = 4 * work <= kFewQuadrants || (a.max_width > 32 && a.pairs >= kLongLists * work);
   if (multi) {
     // one wave per half tile: two per tile, whole rounds of 8 XCDs
     const int64_t pblocks = ((int64_t)a.tiles_stride * m + 7) / 8 * 16;
@@ -1194,7 +1205,9 @@ hipError_t launch_blend_t(const BlendArgs& a, int m, hipStream_t s) {
                        a.ids, a.ranges, a.geom, a.n, a.tiles_stride, m, a.sets, a.groups,
                        a.ngroups);
   } else
-    hipLaunchKernelGGL((two ? blend_wide_kernel<DT, PX, true> : blend_wide_kernel<DT, PX, false>),
+    hipLaunchKernelGGL((two                ? blend_wide_kernel<DT, PX, true, 2>
+                        : a.max_width > 32 ? blend_wide_kernel<DT, PX, false, 2>
+                                           : blend_wide_kernel<DT, PX, false, 1>),
                        dim3((unsigned)blocks), dim3(two ? 128 : 64), 0, s, a.rec, a.ids, a.ranges, a.geom, a.n,
                        a.tiles_stride, m, a.sets, a.groups, a.ngroups);
   return hipGetLastError();

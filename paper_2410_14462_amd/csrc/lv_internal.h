@@ -251,6 +251,7 @@ struct BlendArgs {
   const SetDesc* sets;         // device
   const ChanGroup* groups;     // device (wide kernel)
   int32_t ngroups;
+  int64_t pairs;               // (tile, Gaussian) pairs of the launch
   int32_t max_width;           // widest group; 0: tail channels only
   int32_t has_tail;            // the last group has tail channels
 };

@@ -1,6 +1,6 @@
-"""The one-wave form of the one-group blend (more than 4096 quadrants, at most 32
-channels) in every element type and layout, with sets that skip views, and the
-deterministic accumulator in both forms.  Reference: the FP64 oracle on the maps
+"""The one-wave forms of the one-group blend (more than 4096 quadrants and at most
+32 channels, or short lists) in every element type and layout, with sets that
+skip views, and the deterministic accumulator in both forms.  Reference: the FP64 oracle on the maps
 as stored (decoded on the CPU), with the bars of the uplift tests."""
 import numpy as np
 import pytest
@@ -50,6 +50,30 @@ def test_one_wave_storage(scene, D, elem, layout):
     acc.add(cams, [m], dtype=elem + layout, scales=None if scales is None else scales.view(1, D))
     f, b = acc.finalize()
     c = acc.counts().cpu().numpy().astype(np.int64)
+    acc.close()
+    ref = oracle.uplift(sc, cams, [ref_map.cpu().numpy()])
+    assert feature_error(f.cpu().numpy(), ref).max(initial=0.0) < 1e-4
+    assert beta_error(b.cpu().numpy(), ref).max(initial=0.0) < 1e-4
+    assert counts_match(c, ref)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "fp8", "f32_px8", "bf16_px8", "fp8_px8"])
+@pytest.mark.parametrize("n", [500, 20_000])  # lists below and above the rule's 128 in the mean
+@pytest.mark.parametrize("D", [33, 64, 67])
+def test_wide_groups_short_and_long_lists(D, n, dtype):
+    sc = scenes.make_scene(78, n, -3.2, 0.5, -2.0, 1.0)
+    gs = lv.Scene.from_arrays(sc)
+    cams = cameras(1)
+    print(f"lists n={n} D={D} {dtype}", flush=True)
+    x = torch.as_tensor(scenes.map_uniform(79, 0, H, W, D), device="cuda")
+    ref_map, scales = stored(x, dtype.split("_")[0])
+    m = x if dtype == "f32" else lv.encode(x, dtype)[0]
+    acc = lv.Accum(gs, D, counts=True)
+    acc.add(cams, [m], dtype=dtype, scales=None if scales is None else scales.view(1, D))
+    f, b = acc.finalize()
+    c = acc.counts().cpu().numpy().astype(np.int64)
+    tiles = ((W + 15) // 16) * ((H + 15) // 16)
+    assert (acc.stats()["pairs"] >= 128 * tiles) == (n > 500)
     acc.close()
     ref = oracle.uplift(sc, cams, [ref_map.cpu().numpy()])
     assert feature_error(f.cpu().numpy(), ref).max(initial=0.0) < 1e-4
