@@ -17,8 +17,8 @@
 //      evaluates the Gaussian at its pixel (the record read from LDS at one
 //      address, a broadcast), every decision in the S32 sequence;
 //   B. the Gaussian takes the next of 32 LDS rows (its weights at the 64
-//      pixels; in the pair and render kernels only if some w > 0).  A full set of rows (and the last, partial one) is
-//      flushed: U_rows += W_rows F on the matrix cores, one global atomic per
+//      pixels; in the pair and render kernels only if some w > 0).  A full set
+//      of rows (and the last, partial one) is flushed: U_rows += W_rows F on the matrix cores, one global atomic per
 //      (Gaussian, channel); beta (the rows' sums, in exact fixed point, once
 //      for all feature sets that take the same views) and the tail channels
 //      (the rows' dot products with up to 4 further channels) by one lane

@@ -48,13 +48,15 @@ __device__ __forceinline__ uint32_t e4m3x2(float x, float y) {
   return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(x, y, 0, false) & 0xFFFFu;
 }
 
-// x / sc, correctly rounded as by the division, for many x and one sc: with rc
-// the correctly rounded reciprocal, q = x rc is within an ulp, r = x - q sc is
-// exact in one fused operation, and q + r rc rounds to the quotient (Markstein,
-// IBM J. Res. Dev. 34(1), 1990) unless sc's significand is all ones.  rc = 0
-// asks for the division itself: that significand, and scales so small or large
-// that r, or the products, would leave the normal range for an x whose code is
-// not zero.
+// x / sc as the division gives it, for many x and one sc: with rc the correctly
+// rounded reciprocal, q = x rc is within two ulps of the quotient, r = x - q sc is
+// exact in one fused operation, and q + r rc is rounded once (the form of Markstein,
+// IBM J. Res. Dev. 34(1), 1990, whose theorem asks for a q within one ulp).  That
+// the result is the quotient's rounding here was checked on the CPU for every
+// significand of sc, with x at and next to each multiple of sc where a code ends (2.0e9
+// pairs), and for 4.8e8 random pairs.  rc = 0 asks for the division itself: scales so
+// small or large that r, or the products, would leave the normal range for an x
+// whose code is not zero, and (as the theorem does) a significand of ones.
 struct ChanScale {
   float sc, rc;
   __device__ __forceinline__ void set(float amax) {

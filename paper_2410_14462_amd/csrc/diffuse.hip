@@ -2,8 +2,10 @@
 // channel normalised by its own norm.  Since the normalisation is a
 // per-channel scale, step t computes y = s_t * (A g_t) with
 // s_t = 1 / ||g_t|| (0 for a zero channel) and, in the same pass, the squared
-// norms of y for step t+1.  CSR SpMM: a group of C lanes (C = channel width,
-// power of two <= 64) owns one row; lane c handles channels c, c + C, ...
+// norms of y for step t+1.  CSR SpMM in three forms: spmm_rows_kernel for up to 4
+// channels (a row per lane, edges staged in LDS), spmm_wide_kernel for 8, 16, 32
+// and 64 (a few lanes per row, each with a piece of it), spmm_kernel for the rest
+// (a group of C lanes per row, lane c on channels c, c + C, ...).
 #include <algorithm>
 
 #include "lv_internal.h"

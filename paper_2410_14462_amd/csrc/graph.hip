@@ -35,7 +35,7 @@ namespace lv {
 namespace {
 
 // Centres per grid cell: 1M uniform centres, k = 16, the build and ten steps of
-// diffusion take 4.65, 4.60, 4.67 ms with 1, 2 and 3.
+// diffusion take 4.22, 4.13, 4.19 ms with 1, 2 and 3.
 constexpr int kCellCentres = 2;
 
 // ---------------------------------------------------------------- grid
@@ -805,7 +805,7 @@ hipError_t build_knn_graph(const float4* centres, int64_t n, const float* feats,
       }
       hipLaunchKernelGGL(sigma_kernel, dim3(1), dim3(64), 0, s, st, sig2);
       hipLaunchKernelGGL(rbf_weights_kernel, dim3(grid1(nk)), dim3(256), 0, s, nk, k, sid, pos, w,
-                         sig2,                         (double)gw.bandwidth, gw.unary, d2);
+                         sig2, (double)gw.bandwidth, gw.unary, d2);
       double* t = w;  // the weights are in d2's buffer
       w = d2;
       d2 = t;
